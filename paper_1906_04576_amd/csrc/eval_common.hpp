@@ -94,6 +94,19 @@ __device__ __forceinline__ ChunkRange chunk_range(unsigned nchunks) {
     return {lo + k, hi, per};
 }
 
+// The naive pass: one dense level, its item count known to the host.  One
+// block per chunk, chunks in contiguous shares per XCD, so that the hardware
+// hands a new chunk to whichever wave slots fall free.  (A resident grid with
+// an equal number of chunks per block ended unevenly: the SIMDs favour their
+// oldest waves, and the last blocks ran for a third of the launch with their
+// neighbours' slots empty.)
+__host__ __device__ __forceinline__ bool one_dense_level(const EvalCommon& c) { return c.nlev == 1 && !c.lv[0].list; }
+
+__device__ __forceinline__ ChunkRange naive_chunk(unsigned nchunks) {
+    const unsigned b = xcd_remap(blockIdx.x, gridDim.x);
+    return {b, min(nchunks, b + 1u), 1u};
+}
+
 // Chunks of a launch's item space handed to its blocks.  Q false: each block
 // takes a fixed stride of its XCD's region (chunk_range).  Q true: the blocks
 // of an XCD take that region's chunks one at a time from the XCD's counter
@@ -155,56 +168,77 @@ __device__ __forceinline__ void batch_chunk_bases(const Args* T, int n, unsigned
 // instead of a vector load (and its full wait) per sample.
 constexpr int kLdsSamples = 1024;
 
-// a_i at every listed texel: the separable blur of the dense path with the
-// zero terms left out (g * 0 = +0 and acc + 0 = acc, so the sums are equal).
-// The radius is a template parameter so that all 2R+1 rows' words are loaded
-// in one batch.
+// a_i at a listed texel: the separable blur of the dense path with the zero
+// terms left out or added as +0 (g * 0 = +0 and acc + 0 = acc, so the sums
+// are equal).  A row's sum over its 2R + 1 edge bits takes the low kRowBits
+// bits from a table in LDS (row_table: the sums of the first taps in
+// ascending order) and adds the taps of the others one by one.  All words
+// are loaded first, then all table entries: one memory and one LDS latency
+// per texel.  (A loop over the set bits with the taps read from LDS made the
+// wave wait for its lane with the most bits, an LDS latency per bit: 1.2 to 6
+// us of an 8 to 12 us wave on a 256 x 256 frame.)
+constexpr int kRowBits = 8, kRowTable = 1 << kRowBits;
+constexpr int kRowLevels = 3;  // list levels of the compact path
+
 template <int R>
-__device__ __forceinline__ float alpha_at(const uint32_t* Eb, int wpr, int H, const float* g, int x, int y) {
+__device__ __forceinline__ float alpha_at(const EvalLevel& L, const float* rows, int x, int y) {
     constexpr int N = 2 * R + 1;
-    const int x0 = x - R;
-    const int w0 = x0 >> 5, sh = x0 & 31;
-    const bool lo_ok = w0 >= 0 && w0 < wpr, hi_ok = w0 + 1 >= 0 && w0 + 1 < wpr;
+    const int x0 = x - R, w0 = x0 >> 5;
+    const unsigned pitch = 4u * (unsigned)L.Ewpr;
+    // Words off the level read as 0: past the end of the buffer, a load
+    // returns 0 without an access.
+    const __amdgpu_buffer_rsrc_t re = buf_rsrc(L.Eb, pitch * (unsigned)L.H);
+    const unsigned lo_off = w0 >= 0 ? 4u * (unsigned)w0 : 0x80000000u;
+    const unsigned hi_off = w0 + 1 < L.Ewpr ? 4u * (unsigned)(w0 + 1) : 0x80000000u;
     unsigned lo[N], hi[N];
 #pragma unroll
     for (int ky = 0; ky < N; ++ky) {
-        const int yy = y - R + ky;
-        const bool rok = yy >= 0 && yy < H;
-        const uint32_t* row = Eb + (unsigned)(rok ? yy : 0) * (unsigned)wpr;
-        lo[ky] = (rok && lo_ok) ? row[w0] : 0u;
-        hi[ky] = (rok && hi_ok) ? row[w0 + 1] : 0u;
+        const unsigned row = (unsigned)(y - R + ky) * pitch;
+        lo[ky] = __builtin_amdgcn_raw_buffer_load_b32(re, lo_off + row, 0, 0);
+        hi[ky] = __builtin_amdgcn_raw_buffer_load_b32(re, hi_off + row, 0, 0);
+    }
+    float h[N];
+    unsigned m[N];
+#pragma unroll
+    for (int ky = 0; ky < N; ++ky) {
+        m[ky] = __builtin_amdgcn_alignbit(hi[ky], lo[ky], (unsigned)x0 & 31u);
+        if (N < 32) m[ky] &= (1u << N) - 1u;
+        h[ky] = rows[m[ky] & (kRowTable - 1u)];
     }
     float a = 0.0f;
 #pragma unroll
     for (int ky = 0; ky < N; ++ky) {
-        unsigned m = sh ? (lo[ky] >> sh) | (hi[ky] << (32 - sh)) : lo[ky];
-        m &= (1u << N) - 1u;
-        if (!m) continue;
-        float h = 0.0f;
-        while (m) {
-            const int k = __builtin_ctz(m);
-            m &= m - 1;
-            h = h + g[k];
-        }
-        a = a + g[ky] * h;
+#pragma unroll
+        for (int k = kRowBits; k < N; ++k)
+            h[ky] = h[ky] + __uint_as_float(__float_as_uint(L.Eg[k]) & (unsigned)__builtin_amdgcn_sbfe((int)m[ky], k, 1));
+        a = a + L.Eg[ky] * h[ky];
     }
     return a;
 }
 
-// blur taps of every level in LDS (the caller synchronises before use)
-constexpr int kEgStride = 2 * kBlurFusedMaxRadiusC + 1;
-__device__ __forceinline__ void stage_taps(const EvalCommon& c, float* eg) {
-    for (int i = threadIdx.x; i < kMaxLevels * kEgStride; i += blockDim.x) {
-        const int j = i / kEgStride, k = i - j * kEgStride;
-        eg[i] = c.lv[j].Eg[k];
+// tables of the list levels' row sums in LDS (the caller synchronises before
+// use); blocks of at least kRowTable threads
+__device__ __forceinline__ void stage_rows(const EvalCommon& c, float* rows) {
+    const unsigned m = threadIdx.x;
+    if (m >= (unsigned)kRowTable) return;
+#pragma unroll
+    for (int j = 0; j < kRowLevels; ++j) {
+        if (!c.lv[j].ac) continue;
+        float h = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kRowBits; ++k)
+            h = h + __uint_as_float(__float_as_uint(c.lv[j].Eg[k]) & (unsigned)__builtin_amdgcn_sbfe((int)m, k, 1));
+        rows[j * kRowTable + (int)m] = h;
     }
 }
 
-// a_i of a listed texel for the evaluators (radius <= 8, else 0)
-__device__ __forceinline__ float alpha_dispatch(const EvalLevel& L, const float* g, int x, int y) {
+// a_i of a listed texel of level slot j for the evaluators (radius <= 8,
+// else 0)
+__device__ __forceinline__ float alpha_dispatch(const EvalLevel& L, const float* rows, int j, int x, int y) {
+    const float* t = rows + j * kRowTable;
     switch (L.Er) {
 #define MR_ALPHA(R) \
-    case R: return alpha_at<R>(L.Eb, L.Ewpr, L.H, g, x, y);
+    case R: return alpha_at<R>(L, t, x, y);
         MR_ALPHA(0) MR_ALPHA(1) MR_ALPHA(2) MR_ALPHA(3) MR_ALPHA(4) MR_ALPHA(5) MR_ALPHA(6) MR_ALPHA(7) MR_ALPHA(8)
 #undef MR_ALPHA
         default: return 0.0f;
@@ -303,6 +337,12 @@ __host__ inline unsigned eval_blocks(unsigned total_hint) {
     if (b > cap) b = cap;
     if (b < 1) b = 1;
     return b;
+}
+
+// grid of an evaluation pass: one block per chunk of a naive pass
+template <auto Kernel>
+__host__ inline unsigned eval_grid(const EvalCommon& c, unsigned total_hint) {
+    return one_dense_level(c) ? (c.lv[0].dense_n + 255u) / 256u : eval_blocks<Kernel>(total_hint);
 }
 
 // compute units of the current device, queried once per device

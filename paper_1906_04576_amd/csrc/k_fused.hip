@@ -122,7 +122,7 @@ template <int EFFECT, typename NT, typename CT, bool M4>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_batch_fused(FusedArgs A) {
     constexpr int C = EFFECT == MR_EFFECT_SSGI ? 3 : 1;
     __shared__ float ks[3 * kFusedSamples];
-    __shared__ float eg[kMaxLevels * kEgStride];
+    __shared__ float rows[kRowLevels * kRowTable];
     __shared__ FusedLds<C> u;
     __shared__ unsigned slot;
     // tb[s][f]: frame f's first ticket of stage s, relative to the stage
@@ -133,9 +133,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     __shared__ unsigned tb[kFusedStages][kMaxBatchFrames + 1];
     float kmax = 0.0f;
     if constexpr (EFFECT == MR_EFFECT_SSAO) {
-        kmax = ssao_stage<true, true>(static_cast<const SsaoArgs*>(A.tv)[0], ks, eg);
+        kmax = ssao_stage<true, true>(static_cast<const SsaoArgs*>(A.tv)[0], ks, rows);
     } else {
-        ssgi_stage<true, true>(static_cast<const SsgiArgs*>(A.tv)[0], ks, eg);
+        kmax = ssgi_stage<true, true>(static_cast<const SsgiArgs*>(A.tv)[0], ks, rows);
     }
     const unsigned G = (unsigned)A.group;
     if (threadIdx.x < 64) {
@@ -226,9 +226,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                         const unsigned item = c * per + (unsigned)i * 256u + threadIdx.x;
                         if (item >= items) continue;
                         if constexpr (EFFECT == MR_EFFECT_SSAO)
-                            ssao_item<NT, true, true>(a, m, item, ks, eg, kmax);
+                            ssao_item<NT, true, true>(a, m, item, ks, rows, kmax);
                         else
-                            ssgi_item<NT, CT, true>(a, m, item, (const float*)ks, (const float*)eg);
+                            ssgi_item<NT, CT, true>(a, m, item, (const float*)ks, kmax, (const float*)rows);
                     }
                 }
             }

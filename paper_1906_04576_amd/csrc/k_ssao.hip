@@ -10,9 +10,9 @@ namespace mr {
 template <typename NT, bool AL, bool KLDS>
 __global__ __launch_bounds__(256) void k_ssao(SsaoArgs a) {
     __shared__ float ks[KLDS ? 3 * kLdsSamples : 1];
-    __shared__ float eg[kMaxLevels * kEgStride];
-    const float kmax = ssao_stage<AL, KLDS>(a, ks, eg);
-    ssao_items<NT, KLDS, AL>(a, ks, eg, kmax);
+    __shared__ float rows[kRowLevels * kRowTable];
+    const float kmax = ssao_stage<AL, KLDS>(a, ks, rows);
+    ssao_items<NT, KLDS, AL>(a, ks, rows, kmax);
 }
 
 // The compact frame path with the coarsest level in 16 x 16 tiles whose depth
@@ -21,10 +21,10 @@ __global__ __launch_bounds__(256) void k_ssao(SsaoArgs a) {
 template <typename NT, int H>
 __global__ __launch_bounds__(256) void k_ssao_tiled(SsaoArgs a) {
     __shared__ float ks[3 * kTiledSamples];
-    __shared__ float eg[kMaxLevels * kEgStride];
+    __shared__ float rows[kRowLevels * kRowTable];
     __shared__ float zt[(kDenseTile + 2 * H) * (kDenseTile + 2 * H)];
-    const float kmax = ssao_stage<true, true>(a, ks, eg);
-    ssao_items_tiled<NT, H>(a, ks, eg, kmax, zt);
+    const float kmax = ssao_stage<true, true>(a, ks, rows);
+    ssao_items_tiled<NT, H>(a, ks, rows, kmax, zt);
 }
 
 // Frames of a batch (same samples, mask and effect parameters): one item
@@ -33,9 +33,9 @@ __global__ __launch_bounds__(256) void k_ssao_tiled(SsaoArgs a) {
 template <typename NT, bool AL, bool KLDS, bool Q>
 __global__ __launch_bounds__(256) void k_ssao_batch(const SsaoArgs* __restrict__ T, int n, unsigned* queue) {
     __shared__ float ks[KLDS ? 3 * kLdsSamples : 1];
-    __shared__ float eg[kMaxLevels * kEgStride];
+    __shared__ float rows[kRowLevels * kRowTable];
     __shared__ unsigned cbase[kMaxBatch + 1];
-    const float kmax = ssao_stage<AL, KLDS>(T[0], ks, eg);
+    const float kmax = ssao_stage<AL, KLDS>(T[0], ks, rows);
     batch_chunk_bases(T, n, 256u, cbase);
     for_each_chunk<Q>(cbase[n], queue, [&](unsigned c) {
         int f = 0;
@@ -43,7 +43,7 @@ __global__ __launch_bounds__(256) void k_ssao_batch(const SsaoArgs* __restrict__
         const SsaoArgs& a = T[f];
         const ItemMap m = make_item_map(a.c);
         const unsigned item = (c - cbase[f]) * 256u + threadIdx.x;
-        if (item < item_total(m)) ssao_item<NT, KLDS, AL>(a, m, item, ks, eg, kmax);
+        if (item < item_total(m)) ssao_item<NT, KLDS, AL>(a, m, item, ks, rows, kmax);
     });
 }
 
@@ -143,13 +143,14 @@ __global__ __launch_bounds__(256) void k_ssao_fullres(FullresArgs a) {
     const NT* nrm = static_cast<const NT*>(a.normal);
     const unsigned plane = (unsigned)a.plane, npx = (unsigned)a.W * (unsigned)a.H;
     const int top = a.nlev - 1;  // the coarsest level
-    const ChunkRange cr = chunk_range((npx + 255u) / 256u);
+    const ChunkRange cr = naive_chunk((npx + 255u) / 256u);
     for (unsigned ch = cr.first; ch < cr.end; ch += cr.step) {
         const unsigned p = ch * 256u + threadIdx.x;
         const bool in = p < npx;
         const int y = in ? (int)(p / (unsigned)a.W) : 0, x = in ? (int)(p - (unsigned)y * (unsigned)a.W) : 0;
         const float z = in ? L.z[(unsigned)y * L.zpy + (unsigned)x * L.zpx] : 0.0f;
         const bool geo = in && valid_depth(z);
+        const Normal n = texel_normal(L, nrm, plane, x, y);
         // alpha of the levels below the coarsest (registers: constant indices)
         float al[kMaxLevels - 1];
         int k = top;  // finest level with alpha 1, else the coarsest
@@ -169,8 +170,8 @@ __global__ __launch_bounds__(256) void k_ssao_fullres(FullresArgs a) {
             const bool need = geo && (j == k || (j < k && alj > 0.0f));
             if (__ballot(need) == 0) continue;
             if (need) {
-                const float v = ssao_texel<NT, kGroupPlain>(sp[j], L, nrm, plane, (const float*)ks + 3 * skoff[j],
-                                                     __uint_as_float(kmax_bits[j]), x, y, z);
+                const float v = ssao_texel(sp[j], L, n, (const float*)ks + 3 * skoff[j],
+                                           __uint_as_float(kmax_bits[j]), x, y, z);
                 c = j == k ? v : v * alj + c * (1.0f - alj);
             }
         }
@@ -181,11 +182,9 @@ __global__ __launch_bounds__(256) void k_ssao_fullres(FullresArgs a) {
 hipError_t launch_ssao_fullres(const FullresArgs& a, int normal_dtype, hipStream_t s) {
     const unsigned chunks = ((unsigned)a.W * (unsigned)a.H + 255u) / 256u;
     if (normal_dtype == MR_F16)
-        hipLaunchKernelGGL((k_ssao_fullres<_Float16>), dim3(eval_blocks<k_ssao_fullres<_Float16>>(chunks * 256u)),
-                           dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_ssao_fullres<_Float16>), dim3(chunks), dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL((k_ssao_fullres<float>), dim3(eval_blocks<k_ssao_fullres<float>>(chunks * 256u)),
-                           dim3(256), 0, s, a);
+        hipLaunchKernelGGL((k_ssao_fullres<float>), dim3(chunks), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -215,7 +214,7 @@ hipError_t launch_ssao(const SsaoArgs& a, int normal_dtype, unsigned total_hint,
         return hipGetLastError();
     }
 #define MR_SSAO(NT, AL, KL) \
-    hipLaunchKernelGGL((k_ssao<NT, AL, KL>), dim3(eval_blocks<k_ssao<NT, AL, KL>>(total_hint)), dim3(256), 0, s, a)
+    hipLaunchKernelGGL((k_ssao<NT, AL, KL>), dim3(eval_grid<k_ssao<NT, AL, KL>>(a.c, total_hint)), dim3(256), 0, s, a)
     if (normal_dtype == MR_F16) {
         if (al) {
             if (lds) MR_SSAO(_Float16, true, true);

@@ -13,17 +13,17 @@ namespace mr {
 template <typename NT, int H>
 __global__ __launch_bounds__(256) void k_ssao_batch_tiled(const SsaoArgs* __restrict__ T, int n) {
     __shared__ float ks[3 * kTiledSamples];
-    __shared__ float eg[kMaxLevels * kEgStride];
+    __shared__ float rows[kRowLevels * kRowTable];
     __shared__ float zt[(kDenseTile + 2 * H) * (kDenseTile + 2 * H)];
     __shared__ unsigned cbase[kMaxBatch + 1];
-    const float kmax = ssao_stage<true, true>(T[0], ks, eg);
+    const float kmax = ssao_stage<true, true>(T[0], ks, rows);
     batch_chunk_bases<true>(T, n, 256u, cbase);
     const ChunkRange cr = chunk_range(cbase[n]);
     for (unsigned c = cr.first; c < cr.end; c += cr.step) {
         int f = 0;
         for (int k = 1; k < n; ++k) f += c >= cbase[k] ? 1 : 0;
         const SsaoArgs& a = T[f];
-        ssao_chunk_tiled<NT, H>(a, make_item_map<true>(a.c), c - cbase[f], ks, eg, kmax, zt);
+        ssao_chunk_tiled<NT, H>(a, make_item_map<true>(a.c), c - cbase[f], ks, rows, kmax, zt);
     }
 }
 

@@ -9,21 +9,24 @@ namespace mr {
 template <typename NT, typename CT, bool AL, bool KLDS>
 __global__ __launch_bounds__(256) void k_ssgi(SsgiArgs a) {
     __shared__ float ks[KLDS ? 3 * kLdsSamples : 1];
-    __shared__ float eg[kMaxLevels * kEgStride];
-    ssgi_stage<AL, KLDS>(a, ks, eg);
+    __shared__ float rows[kRowLevels * kRowTable];
+    const float kmax = ssgi_stage<AL, KLDS>(a, ks, rows);
     if (KLDS)
-        ssgi_items<NT, CT, AL>(a, (const float*)ks, (const float*)eg);
+        ssgi_items<NT, CT, AL>(a, (const float*)ks, kmax, (const float*)rows);
     else
-        ssgi_items<NT, CT, AL>(a, a.kernel, (const float*)eg);
+        ssgi_items<NT, CT, AL>(a, a.kernel, kmax, (const float*)rows);
 }
 
-// frames of a batch (see k_ssao_batch)
+// Frames of a batch (see k_ssao_batch).  Four waves per SIMD: the frames'
+// gathers share the caches, and more waves lose more in them than they hide
+// (8 uneven frames, 64 samples: 904, 872, 899 and 922 us with 3, 4, 5 and 8
+// waves; a frame alone is fastest with all that fit).
 template <typename NT, typename CT, bool Q, bool KLDS>
-__global__ __launch_bounds__(256) void k_ssgi_batch(const SsgiArgs* __restrict__ T, int n, unsigned* queue) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ssgi_batch(const SsgiArgs* __restrict__ T, int n, unsigned* queue) {
     __shared__ float ks[KLDS ? 3 * kLdsSamples : 1];
-    __shared__ float eg[kMaxLevels * kEgStride];
+    __shared__ float rows[kRowLevels * kRowTable];
     __shared__ unsigned cbase[kMaxBatch + 1];
-    ssgi_stage<true, KLDS>(T[0], ks, eg);
+    const float kmax = ssgi_stage<true, KLDS>(T[0], ks, rows);
     batch_chunk_bases(T, n, 256u, cbase);
     for_each_chunk<Q>(cbase[n], queue, [&](unsigned c) {
         int f = 0;
@@ -33,9 +36,9 @@ __global__ __launch_bounds__(256) void k_ssgi_batch(const SsgiArgs* __restrict__
         const unsigned item = (c - cbase[f]) * 256u + threadIdx.x;
         if (item >= item_total(m)) return;
         if (KLDS)
-            ssgi_item<NT, CT, true>(a, m, item, (const float*)ks, (const float*)eg);
+            ssgi_item<NT, CT, true>(a, m, item, (const float*)ks, kmax, (const float*)rows);
         else
-            ssgi_item<NT, CT, true>(a, m, item, T[0].kernel, (const float*)eg);
+            ssgi_item<NT, CT, true>(a, m, item, T[0].kernel, kmax, (const float*)rows);
     });
 }
 
@@ -77,7 +80,7 @@ hipError_t launch_ssgi(const SsgiArgs& a, int normal_dtype, int color_dtype, uns
                        hipStream_t s) {
     const bool al = fused_alpha(a.c), lds = a.S <= kLdsSamples;
 #define MR_SK(NT, CT, AL, KL) \
-    hipLaunchKernelGGL((k_ssgi<NT, CT, AL, KL>), dim3(eval_blocks<k_ssgi<NT, CT, AL, KL>>(total_hint)), dim3(256), 0, s, a)
+    hipLaunchKernelGGL((k_ssgi<NT, CT, AL, KL>), dim3(eval_grid<k_ssgi<NT, CT, AL, KL>>(a.c, total_hint)), dim3(256), 0, s, a)
 #define MR_SSGI(NT, CT)                \
     do {                               \
         if (al) {                      \

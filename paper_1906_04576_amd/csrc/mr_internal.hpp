@@ -32,12 +32,10 @@ __device__ __forceinline__ void store_stream4(float* p, float a, float b, float 
     __builtin_nontemporal_store(v, reinterpret_cast<f4v*>(p));
 }
 
-// float -> int32 with the conversion instruction's own result for every
-// input (truncation; NaN gives 0, values out of range saturate), where a
-// C++ conversion of such a value is undefined
-__device__ __forceinline__ int cvt_i32_sat(float x) {
+// largest integer not above x (values out of int32's range saturate)
+__device__ __forceinline__ int floor_i32(float x) {
     int r;
-    asm("v_cvt_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
     return r;
 }
 

@@ -6,196 +6,176 @@
 //   v_hat = v / sqrt(dd), g = (max(0, n.v_hat) max(0, -n_t.v_hat)) / dist2,
 //   acc += C_t g;  out = acc (r^2 / S).
 #pragma once
-#include "eval_common.hpp"
+#include "sample_hits.hpp"
 
 namespace mr {
 
-// depth gathers in flight per sample group of the naive pass (measured)
-constexpr int kSsgiGroup = 8;
+// element e of a plane of floats or halves, widened
+template <typename T>
+__device__ __forceinline__ float plane_ld(__amdgpu_buffer_rsrc_t r, unsigned e);
+template <>
+__device__ __forceinline__ float plane_ld<float>(__amdgpu_buffer_rsrc_t r, unsigned e) {
+    return buf_f1(r, e * 4u);
+}
+template <>
+__device__ __forceinline__ float plane_ld<_Float16>(__amdgpu_buffer_rsrc_t r, unsigned e) {
+    return (float)__builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, e * 2u, 0, 0));
+}
+
+// the three planes of a normal or colour image
+template <typename T>
+struct Planes {
+    __amdgpu_buffer_rsrc_t r[3];
+    __device__ __forceinline__ Planes(const T* p, unsigned plane) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) r[c] = buf_rsrc(p + (size_t)c * plane, plane * (unsigned)sizeof(T));
+    }
+    __device__ __forceinline__ void load(unsigned e, float (&o)[3]) const {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = plane_ld<T>(r[c], e);
+    }
+};
+
+// samples whose depth gathers are in flight together (2, 4 and 8 measured the
+// same: the light's six gathers per hit bound the launches)
+constexpr int kLightGroup = 4;
+
+// What a texel's light gathers from one occluding sample: the texel it hit.
+struct LightHit {
+    int x, y;
+    float z, n[3], c[3];
+};
+
+template <typename NT, typename CT>
+__device__ __forceinline__ void light_load(const EvalLevel& L, const Planes<NT>& nrm, const Planes<CT>& col, LightHit& h) {
+    const unsigned e = (unsigned)L.goff + (unsigned)h.y * (unsigned)L.gpy + (unsigned)h.x * (unsigned)L.gpx;
+    nrm.load(e, h.n);
+    col.load(e, h.c);
+}
+
+__device__ __forceinline__ void light_add(const EvalLevel& L, const SampleTexel& T, const Normal& n, const LightHit& h,
+                                          float rmin2, float (&acc)[3]) {
+    float hx, hy, hz;
+    view_pos(h.x, h.y, h.z, L.f, L.cx, L.cy, hx, hy, hz);
+    const float vx = hx - T.px, vy = hy - T.py, vz = hz - T.pz;
+    const float dd = ((vx * vx) + (vy * vy)) + (vz * vz);
+    if (!(dd > 0.0f)) return;
+    const float dist2 = fmaxf(dd, rmin2);
+    const float il = rsqrt_pos(dd);  // = 1.0f / sqrtf(dd) (dd > 0)
+    const float vhx = vx * il, vhy = vy * il, vhz = vz * il;
+    const float cr = fmaxf(0.0f, ((n.x * vhx) + (n.y * vhy)) + (n.z * vhz));
+    const float ce = fmaxf(0.0f, -(((h.n[0] * vhx) + (h.n[1] * vhy)) + (h.n[2] * vhz)));
+    const float w = (cr * ce) / dist2;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[c] = acc[c] + h.c[c] * w;
+}
+
+// The light of N samples from s: which of them occlude, the depth gathers of
+// all in flight together, then sample by sample the light by the lanes that
+// it occludes, the gathers of two samples in flight together.  All lanes are
+// at the same sample, so that their gathers stay close together: lanes that
+// each worked through their own hits (found for 32 samples before) gathered
+// all over the image and ran the multi-resolution launches 12 % slower.
+template <bool FAST, int N, typename NT, typename CT, typename KP>
+__device__ __forceinline__ void light_group(const SsgiArgs& a, const EvalLevel& L, const SampleTexel& T, const Normal& n,
+                                            KP K, int s, __amdgpu_buffer_rsrc_t rz, const Planes<NT>& np,
+                                            const Planes<CT>& cp, float rmin2, float (&acc)[3]) {
+    float zs[N], d[N];
+    unsigned xy[N];
+    bool hit[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        unsigned off;
+        int x, y;
+        if constexpr (FAST)
+            project_fast(L, K, s + k, T, d[k], off, x, y);
+        else
+            project_any(L, K, s + k, T, hit[k], d[k], off, x, y);
+        zs[k] = buf_f1(rz, off);
+        xy[k] = __builtin_amdgcn_perm((unsigned)y, (unsigned)x, 0x05040100u);  // on screen both fit 16 bits
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        hit[k] = FAST ? (int)occludes_fast(T.z, d[k], zs[k], a.r, a.b) < 0
+                      : occludes_any(hit[k], T.z, d[k], zs[k], a.r, a.b);
+#pragma unroll
+    for (int k = 0; k < N; k += 2) {
+        constexpr int P = N > 1 ? 2 : 1;  // samples at a time
+        LightHit h[P];
+#pragma unroll
+        for (int q = 0; q < P; ++q)
+            if (hit[k + q]) {
+                h[q].x = (int)(xy[k + q] & 0xFFFFu), h[q].y = (int)(xy[k + q] >> 16), h[q].z = zs[k + q];
+                light_load(L, np, cp, h[q]);
+            }
+#pragma unroll
+        for (int q = 0; q < P; ++q)
+            if (hit[k + q]) light_add(L, T, n, h[q], rmin2, acc);
+    }
+}
+
+template <bool FAST, typename NT, typename CT, typename KP>
+__device__ __forceinline__ void ssgi_texel(const SsgiArgs& a, const EvalLevel& L, const SampleTexel& T, const Normal& n,
+                                           KP K, float (&acc)[3]) {
+    const Planes<NT> np(static_cast<const NT*>(a.c.normal), (unsigned)a.c.plane);
+    const Planes<CT> cp(static_cast<const CT*>(a.c.color), (unsigned)a.c.plane);
+    const __amdgpu_buffer_rsrc_t rz = buf_rsrc(L.z, last_texel(L) + 4u);
+    const float rmin = 0.1f * a.r;
+    const float rmin2 = rmin * rmin;
+    constexpr int N = FAST ? kLightGroup : 1;
+    int s = 0;
+    for (; s + N <= a.S; s += N) light_group<FAST, N>(a, L, T, n, K, s, rz, np, cp, rmin2, acc);
+    if constexpr (N > 1)
+        for (; s < a.S; ++s) light_group<FAST, 1>(a, L, T, n, K, s, rz, np, cp, rmin2, acc);
+}
 
 // one item (a listed texel, or a texel of a dense level)
 template <typename NT, typename CT, bool AL, typename KP>
-__device__ __forceinline__ void ssgi_item(const SsgiArgs& a, const ItemMap& m, unsigned item, KP K,
-                                          const float* eg) {
-    const NT* nrm = static_cast<const NT*>(a.c.normal);
-    const CT* col = static_cast<const CT*>(a.c.color);
-    const long long plane = a.c.plane;
-    const float r = a.r, b = a.b;
-    const int S = a.S;
-    const float rmin = 0.1f * r;
-    const float rmin2 = rmin * rmin;
-    const float scale = (r * r) / (float)S;
-    {
-        const int j = item_level(m, item);
-        const EvalLevel& L = a.c.lv[j];
-        const unsigned local = item_local(m, item, j);
-        if (local == ~0u) return;  // padding of the level's item range
-        const unsigned t = L.list ? L.list[local] : local;
-        if (t >= L.dense_n) return;  // malformed list entry
-        const int y = (int)(t / (unsigned)L.W), x = (int)(t - (unsigned)y * (unsigned)L.W);
-        if (AL && L.ac) L.ac[local] = alpha_dispatch(L, eg + j * kEgStride, x, y);
-        const float z = L.z[(unsigned)y * L.zpy + (unsigned)x * L.zpx];
-        float acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f;
-        if (valid_depth(z)) {
-            const long long g = L.goff + (long long)y * L.gpy + (long long)x * L.gpx;
-            const float nx = ld(nrm, g), ny = ld(nrm, plane + g), nz = ld(nrm, 2 * plane + g);
-            float px, py, pz;
-            view_pos(x, y, z, L.f, L.cx, L.cy, px, py, pz);
-            float tx, ty, tz, bx, by, bz;
-            onb(nx, ny, nz, tx, ty, tz, bx, by, bz);
-            const float rtx = r * tx, rty = r * ty, rtz = r * tz;
-            const float rbx = r * bx, rby = r * by, rbz = r * bz;
-            const float rnx = r * nx, rny = r * ny, rnz = r * nz;
-            if constexpr (AL) {
-                // multi-resolution launches: one pass over the samples (their
-                // texels sit near edges, where many samples occlude)
-                const float Wf = (float)L.W, Hf = (float)L.H;
-                for (int s = 0; s < S; ++s) {
-                    const float kx = K[3 * s], ky = K[3 * s + 1], kz = K[3 * s + 2];
-                    const float qx = ((px + kx * rtx) + ky * rbx) + kz * rnx;
-                    const float qy = ((py + kx * rty) + ky * rby) + kz * rny;
-                    const float qz = ((pz + kx * rtz) + ky * rbz) + kz * rnz;
-                    const float d = -qz;
-                    if (!(d > 0.0f)) continue;
-                    const float inv = recip_pos(d);  // = 1.0f / d (d > 0)
-                    const float u = L.cx + (qx * inv) * L.f;
-                    const float v = L.cy - (qy * inv) * L.f;
-                    // 0 <= u < W and 0 <= v < H as unsigned compares of the
-                    // bit patterns: exact, as u = cx + t and v = cy - t' are
-                    // never -0 (cx, cy > 0)
-                    if (!((__float_as_uint(u) < __float_as_uint(Wf)) & (__float_as_uint(v) < __float_as_uint(Hf))))
-                        continue;
-                    const int sx = (int)u, sy = (int)v;  // u, v >= 0: truncation is floor
-                    const float zs = L.z[(unsigned)sy * L.zpy + (unsigned)sx * L.zpx];
-                    if (!valid_depth(zs)) continue;
-                    if (!(zs < d - (b * d) && fabsf(z - zs) < r)) continue;
-                    float hx, hy, hz;
-                    view_pos(sx, sy, zs, L.f, L.cx, L.cy, hx, hy, hz);
-                    const float vx = hx - px, vy = hy - py, vz = hz - pz;
-                    const float dd = ((vx * vx) + (vy * vy)) + (vz * vz);
-                    if (!(dd > 0.0f)) continue;
-                    const float dist2 = fmaxf(dd, rmin2);
-                    const float il = rsqrt_pos(dd);  // = 1.0f / sqrtf(dd) (dd > 0)
-                    const float vhx = vx * il, vhy = vy * il, vhz = vz * il;
-                    const long long gt = L.goff + (long long)sy * L.gpy + (long long)sx * L.gpx;
-                    const float mx = ld(nrm, gt), my = ld(nrm, plane + gt), mz = ld(nrm, 2 * plane + gt);
-                    const float cr = fmaxf(0.0f, ((nx * vhx) + (ny * vhy)) + (nz * vhz));
-                    const float ce = fmaxf(0.0f, -(((mx * vhx) + (my * vhy)) + (mz * vhz)));
-                    const float w = (cr * ce) / dist2;
-                    acc0 = acc0 + ld(col, gt) * w;
-                    acc1 = acc1 + ld(col, plane + gt) * w;
-                    acc2 = acc2 + ld(col, 2 * plane + gt) * w;
-                }
-            } else {
-                const float Wf = (float)L.W, Hf = (float)L.H;
-                // sample s: its point, depth d, and the texel it projects to
-                auto project = [&](int s, float& d, bool& on, int& sx, int& sy) {
-                    const float kx = K[3 * s], ky = K[3 * s + 1], kz = K[3 * s + 2];
-                    const float qx = ((px + kx * rtx) + ky * rbx) + kz * rnx;
-                    const float qy = ((py + kx * rty) + ky * rby) + kz * rny;
-                    const float qz = ((pz + kx * rtz) + ky * rbz) + kz * rnz;
-                    d = -qz;
-                    const float inv = recip_pos(d);  // = 1.0f / d when d > 0 (else unused)
-                    const float u = L.cx + (qx * inv) * L.f;
-                    const float v = L.cy - (qy * inv) * L.f;
-                    on = (d > 0.0f) & (u >= 0.0f) & (u < Wf) & (v >= 0.0f) & (v < Hf);
-                    sx = (int)(on ? u : 0.0f);  // u, v >= 0 when on: truncation is floor
-                    sy = (int)(on ? v : 0.0f);
-                };
-                // L is wave-uniform: the depth plane as a buffer resource
-                const unsigned zpy = (unsigned)L.zpy, zpx = (unsigned)L.zpx;
-                const __amdgpu_buffer_rsrc_t rz =
-                    buf_rsrc(L.z, ((unsigned)(L.H - 1) * zpy + (unsigned)(L.W - 1) * zpx + 1u) * 4u);
-                // a sample adds light iff it occludes: on screen, valid depth
-                // z_s below the biased sample depth and within the radius
-                auto occludes = [&](bool on, float d, float zs) {
-                    return on & (zs > 0.0f) & (zs < d - (b * d)) & (fabsf(z - zs) < r);
-                };
-                // Per block of 32 samples: first which samples occlude (the
-                // depth gathers of kSsgiGroup samples in flight together), then
-                // the light of exactly those samples in sample order, so that
-                // the sums are the ones of one pass over the samples.
-                for (int s0 = 0; s0 < S; s0 += 32) {
-                    const int ns = min(32, S - s0);
-                    unsigned hits = 0u;
-                    int k0 = 0;
-                    for (; k0 + kSsgiGroup <= ns; k0 += kSsgiGroup) {
-                        float d[kSsgiGroup], zs[kSsgiGroup];
-                        bool on[kSsgiGroup];
-                        unsigned off[kSsgiGroup];
-    #pragma unroll
-                        for (int k = 0; k < kSsgiGroup; ++k) {
-                            int sx, sy;
-                            project(s0 + k0 + k, d[k], on[k], sx, sy);
-                            off[k] = __umul24((unsigned)sy, zpy) + __umul24((unsigned)sx, zpx);
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-    #pragma unroll
-                        for (int k = 0; k < kSsgiGroup; ++k) zs[k] = buf_f1(rz, off[k] * 4u);
-    #pragma unroll
-                        for (int k = 0; k < kSsgiGroup; ++k) hits |= occludes(on[k], d[k], zs[k]) ? 1u << (k0 + k) : 0u;
-                    }
-                    for (; k0 < ns; ++k0) {
-                        float d;
-                        bool on;
-                        int sx, sy;
-                        project(s0 + k0, d, on, sx, sy);
-                        const float zs = buf_f1(rz, (__umul24((unsigned)sy, zpy) + __umul24((unsigned)sx, zpx)) * 4u);
-                        hits |= occludes(on, d, zs) ? 1u << k0 : 0u;
-                    }
-                    while (hits) {
-                        const int k = __builtin_ctz(hits);
-                        hits &= hits - 1;
-                        float d;
-                        bool on;
-                        int sx, sy;
-                        project(s0 + k, d, on, sx, sy);
-                        const float zs = L.z[(unsigned)sy * zpy + (unsigned)sx * zpx];
-                        float hx, hy, hz;
-                        view_pos(sx, sy, zs, L.f, L.cx, L.cy, hx, hy, hz);
-                        const float vx = hx - px, vy = hy - py, vz = hz - pz;
-                        const float dd = ((vx * vx) + (vy * vy)) + (vz * vz);
-                        if (!(dd > 0.0f)) continue;
-                        const float dist2 = fmaxf(dd, rmin2);
-                        const float il = rsqrt_pos(dd);  // = 1.0f / sqrtf(dd) (dd > 0)
-                        const float vhx = vx * il, vhy = vy * il, vhz = vz * il;
-                        const long long gt = L.goff + (long long)sy * L.gpy + (long long)sx * L.gpx;
-                        const float mx = ld(nrm, gt), my = ld(nrm, plane + gt), mz = ld(nrm, 2 * plane + gt);
-                        const float cr = fmaxf(0.0f, ((nx * vhx) + (ny * vhy)) + (nz * vhz));
-                        const float ce = fmaxf(0.0f, -(((mx * vhx) + (my * vhy)) + (mz * vhz)));
-                        const float w = (cr * ce) / dist2;
-                        acc0 = acc0 + ld(col, gt) * w;
-                        acc1 = acc1 + ld(col, plane + gt) * w;
-                        acc2 = acc2 + ld(col, 2 * plane + gt) * w;
-                    }
-                }
-            }
-        }
-        const long long o = L.compact ? (long long)local : (long long)y * L.W + x;
-        store_out(L, (unsigned)o, acc0 * scale);
-        store_out(L, (unsigned)L.out_plane + (unsigned)o, acc1 * scale);
-        store_out(L, 2u * (unsigned)L.out_plane + (unsigned)o, acc2 * scale);
+__device__ __forceinline__ void ssgi_item(const SsgiArgs& a, const ItemMap& m, unsigned item, KP K, float kmax,
+                                          const float* rows) {
+    const int j = item_level(m, item);
+    const EvalLevel& L = a.c.lv[j];
+    const unsigned local = item_local(m, item, j);
+    if (local == ~0u) return;  // padding of the level's item range
+    const unsigned t = L.list ? L.list[local] : local;
+    if (t >= L.dense_n) return;  // malformed list entry
+    const int y = (int)(t / (unsigned)L.W), x = (int)(t - (unsigned)y * (unsigned)L.W);
+    // depth and normal are on their way while a_i is computed
+    const float z = L.z[(unsigned)y * L.zpy + (unsigned)x * L.zpx];
+    const Normal n = texel_normal(L, static_cast<const NT*>(a.c.normal), (unsigned)a.c.plane, x, y);
+    if (AL && L.ac) L.ac[local] = alpha_dispatch(L, rows, j, x, y);
+    float acc[3] = {0.0f, 0.0f, 0.0f};
+    if (valid_depth(z)) {
+        const SampleTexel T = sample_texel(L, n, a.r, x, y, z);
+        if (fast_samples(T, kmax, a.r))
+            ssgi_texel<true, NT, CT>(a, L, T, n, K, acc);
+        else
+            ssgi_texel<false, NT, CT>(a, L, T, n, K, acc);
     }
+    const float scale = (a.r * a.r) / (float)a.S;
+    const unsigned o = L.compact ? local : (unsigned)y * (unsigned)L.W + (unsigned)x;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) store_out(L, (unsigned)c * (unsigned)L.out_plane + o, acc[c] * scale);
 }
 
 template <typename NT, typename CT, bool AL, typename KP>
-__device__ __forceinline__ void ssgi_items(const SsgiArgs& a, KP K, const float* eg) {
+__device__ __forceinline__ void ssgi_items(const SsgiArgs& a, KP K, float kmax, const float* rows) {
     const ItemMap m = make_item_map(a.c);
-    const unsigned total = item_total(m);
-    const ChunkRange cr = chunk_range((total + 255) / 256);
+    const unsigned total = item_total(m), nchunks = (total + 255) / 256;
+    const ChunkRange cr = !AL && one_dense_level(a.c) ? naive_chunk(nchunks) : chunk_range(nchunks);
     for (unsigned c = cr.first; c < cr.end; c += cr.step) {
         const unsigned item = c * 256u + threadIdx.x;
-        if (item < total) ssgi_item<NT, CT, AL>(a, m, item, K, eg);
+        if (item < total) ssgi_item<NT, CT, AL>(a, m, item, K, kmax, rows);
     }
 }
 
-// per block: blur taps (AL) and, KLDS, the samples (S <= kLdsSamples)
+// Per block: the blur's row sums (AL) and, KLDS, the samples in LDS; returns
+// the largest |component| of the samples (+inf when not staged).
 template <bool AL, bool KLDS>
-__device__ __forceinline__ void ssgi_stage(const SsgiArgs& a, float* ks, float* eg) {
-    if (AL) stage_taps(a.c, eg);
-    if (KLDS)
-        for (int i = threadIdx.x; i < 3 * a.S; i += 256) ks[i] = a.kernel[i];
-    __syncthreads();
+__device__ __forceinline__ float ssgi_stage(const SsgiArgs& a, float* ks, float* rows) {
+    if (AL) stage_rows(a.c, rows);
+    return stage_samples<KLDS>(a.kernel, a.S, ks);
 }
 
 }  // namespace mr
