@@ -948,9 +948,9 @@ int do_frame_lean(const mr_frame_desc* d, const Geo& g, const void* params, uint
     int st = mark(d, 0, s);
     if (st) return st;
     if (build) {
-        if (P.has_hard && launch_hard(P.ha, s) != hipSuccess)
-            return fail(MR_E_DEVICE, "hard shadow kernel launch failed");
-        if (launch_edges(P.ea, d->g.normal_dtype, s) != hipSuccess) return fail(MR_E_DEVICE, "edge kernel launch failed");
+        const hipError_t e = P.has_hard ? launch_edges_shadow(P.ea, P.ha, d->g.normal_dtype, s)
+                                        : launch_edges(P.ea, d->g.normal_dtype, s);
+        if (e != hipSuccess) return fail(MR_E_DEVICE, "edge kernel launch failed");
         if ((st = mark(d, 4, s))) return st;
         if (launch_lean_masks(P.la, s) != hipSuccess) return fail(MR_E_DEVICE, "lean mask kernels launch failed");
     } else if ((st = mark(d, 4, s))) {

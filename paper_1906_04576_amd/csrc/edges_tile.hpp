@@ -2,7 +2,7 @@
 // level edge bits and the point-sampled level depth: the fast path for
 // widths divisible by 4, shared by the frame, batch and persistent launches.
 #pragma once
-#include "mr_internal.hpp"
+#include "shadow_light.hpp"
 
 namespace mr {
 
@@ -144,7 +144,7 @@ struct EdgeLoads {
 // before any of them is waited for.  (Loading the outer columns after the
 // exchange of the inner ones through LDS put a second memory latency on the
 // outer waves, which the exchange's barrier passed on to the whole block.)
-template <typename NT, bool HARD, bool WIDE>
+template <typename NT, bool HARD, bool WIDE, bool LOAD_HARD = HARD>
 __device__ __forceinline__ void edges_load(const EdgeArgs& a, const EdgeGeom& g, EdgeLoads<NT, HARD>& L) {
     typedef NormalRow<NT> NR;
     const unsigned plane = (unsigned)a.W * (unsigned)a.H;
@@ -152,14 +152,14 @@ __device__ __forceinline__ void edges_load(const EdgeArgs& a, const EdgeGeom& g,
     const NT* nrm = static_cast<const NT*>(a.normal);
     const unsigned nb = plane * NR::kSize;
     const __amdgpu_buffer_rsrc_t rn[3] = {buf_rsrc(nrm, nb), buf_rsrc(nrm + plane, nb), buf_rsrc(nrm + 2 * plane, nb)};
-    const __amdgpu_buffer_rsrc_t rh = buf_rsrc(a.hard, HARD ? plane : 0u);
+    const __amdgpu_buffer_rsrc_t rh = buf_rsrc(a.hard, LOAD_HARD ? plane : 0u);
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const unsigned e = g.ro[r + 1] + (unsigned)g.xc;
         L.z[r] = buf_f4(rz, e * 4u);
 #pragma unroll
         for (int c = 0; c < 3; ++c) L.n[r][c] = NR::ld4(rn[c], e);
-        L.h[r] = HARD ? __builtin_amdgcn_raw_buffer_load_b32(rh, e, 0, 0) : 0u;
+        L.h[r] = LOAD_HARD ? __builtin_amdgcn_raw_buffer_load_b32(rh, e, 0, 0) : 0u;
     }
     const bool top = g.rp == 0, bot = g.rp == 3;
     L.hz = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -171,7 +171,7 @@ __device__ __forceinline__ void edges_load(const EdgeArgs& a, const EdgeGeom& g,
         L.hz = buf_f4(rz, e * 4u);
 #pragma unroll
         for (int c = 0; c < 3; ++c) L.hn[c] = NR::ld4(rn[c], e);
-        if (HARD) L.hh = __builtin_amdgcn_raw_buffer_load_b32(rh, e, 0, 0);
+        if (LOAD_HARD) L.hh = __builtin_amdgcn_raw_buffer_load_b32(rh, e, 0, 0);
     }
 #pragma unroll
     for (int r = 0; r < 2; ++r)
@@ -187,7 +187,43 @@ __device__ __forceinline__ void edges_load(const EdgeArgs& a, const EdgeGeom& g,
                 L.zs[r][sd] = buf_f1(rz, e * 4u);
 #pragma unroll
                 for (int c = 0; c < 3; ++c) L.ns[r][sd][c] = NR::ld1(rn[c], e);
-                if (HARD) L.hs[r][sd] = __builtin_amdgcn_raw_buffer_load_b8(rh, e, 0, 0);
+                if (LOAD_HARD) L.hs[r][sd] = __builtin_amdgcn_raw_buffer_load_b8(rh, e, 0, 0);
+            }
+        }
+}
+
+// The shadow bits of a tile's pixels (and halo) by the one-sample test, in
+// place of loads of a shadow-bit image.
+template <typename NT, bool WIDE>
+__device__ __forceinline__ void edges_hard(const HardArgs& ha, const EdgeGeom& g, EdgeLoads<NT, true>& L) {
+    const __amdgpu_buffer_rsrc_t map = buf_rsrc(ha.sm, 4u * (unsigned)ha.size * (unsigned)ha.size);
+    const float cx = 0.5f * (float)ha.W, cy = 0.5f * (float)ha.H;
+    // view_pos' X and Y of the lane's columns and rows
+    auto column = [&](int x) { return (((float)x + 0.5f) - cx) / ha.f; };
+    auto row = [&](int y) { return (cy - ((float)y + 0.5f)) / ha.f; };
+    float X[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) X[k] = column(g.xb + k);
+    float Y[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        Y[r] = row(g.yb + r);
+        const float z[4] = {L.z[r].x, L.z[r].y, L.z[r].z, L.z[r].w};
+        L.h[r] = hard_bits<4>(ha, map, X, Y[r], z);
+    }
+    const bool top = g.rp == 0, bot = g.rp == 3;
+    if (top || bot) {
+        const float z[4] = {L.hz.x, L.hz.y, L.hz.z, L.hz.w};
+        L.hh = hard_bits<4>(ha, map, X, row(top ? g.yb - 1 : g.yb + 2), z);
+    }
+#pragma unroll
+    for (int sd = 0; sd < 2; ++sd)
+        if (!WIDE || (sd ? g.wave == 3 : g.wave == 0)) {
+            const float xs[1] = {column(sd ? g.x0 + 64 : g.x0 - 1)};
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const float z[1] = {L.zs[r][sd]};
+                L.hs[r][sd] = hard_bits<1>(ha, map, xs, Y[r], z);
             }
         }
 }

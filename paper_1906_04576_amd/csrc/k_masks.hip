@@ -244,6 +244,32 @@ __global__ __launch_bounds__(256) void k_edges_vec(EdgeArgs a, unsigned tiles_x,
     edges_tile<NT, HARD, BITS, WIDE>(a, xcd_remap(blockIdx.x, ntiles), tiles_x);
 }
 
+// The edge image of a soft-shadow frame with the one-sample shadow test of
+// its pixels in the same tile: the depth is read once, and the shadow bits of
+// a 3840 x 2160 frame (a 33 MB read and 8 MB written, then read again) are
+// never stored (a launch of its own for the bits 27 us and the edges 30 us,
+// this one 52 us; 57 us with 134 registers, three waves per SIMD, instead of
+// four).  Bound by the test's arithmetic and the map's gathers.
+template <typename NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_edges_shadow(EdgeArgs a, HardArgs ha, unsigned tiles_x, unsigned ntiles) {
+    const unsigned tile = xcd_remap(blockIdx.x, ntiles);
+    const EdgeGeom g = edge_geom<true>(a, tile, tiles_x);
+    EdgeLoads<NT, true> L;
+    edges_load<NT, true, true, false>(a, g, L);
+    edges_hard<NT, true>(ha, g, L);
+    edges_process<NT, true, true, true>(a, g, tile, L);
+}
+
+hipError_t launch_edges_shadow(const EdgeArgs& a, const HardArgs& ha, int normal_dtype, hipStream_t s) {
+    unsigned tx, n;
+    edges_tiles(a.W, a.H, true, tx, n);
+    if (normal_dtype == MR_F16)
+        hipLaunchKernelGGL(k_edges_shadow<_Float16>, dim3(n), dim3(256), 0, s, a, ha, tx, n);
+    else
+        hipLaunchKernelGGL(k_edges_shadow<float>, dim3(n), dim3(256), 0, s, a, ha, tx, n);
+    return hipGetLastError();
+}
+
 // Frames of a batch: one grid over all frames' tiles (tile_base[f] = first
 // tile of frame f, tile_base[n] = total); tiles_x[f] per frame.  The frame
 // tables of a batch launch are never written while it runs: __restrict__ on

@@ -9,30 +9,9 @@
 // disk of half-width R_s = (l (d_r - n_L)) / (d_r n_L), l = f_L (w_L / 2);
 // penumbra R_f = (l (d_r - d_b)) / (d_b d_r) from the mean blocker depth d_b;
 // visibility = share of PCF taps that are not in front of d_r - bias.
-#include "eval_common.hpp"
+#include "shadow_light.hpp"
 
 namespace mr {
-
-struct LightCoord {
-    float dr, su, sv;
-    bool inside;
-};
-
-__device__ __forceinline__ LightCoord to_light(const float* M, int size, float fL, float px,
-                                               float py, float pz) {
-    const float lx = ((M[0] * px + M[1] * py) + M[2] * pz) + M[3];
-    const float ly = ((M[4] * px + M[5] * py) + M[6] * pz) + M[7];
-    const float lz = ((M[8] * px + M[9] * py) + M[10] * pz) + M[11];
-    LightCoord c;
-    const float cL = 0.5f * (float)size;
-    c.dr = -lz;
-    const float inv = 1.0f / c.dr;
-    c.su = cL + (lx * inv) * fL;
-    c.sv = cL - (ly * inv) * fL;
-    const float sz = (float)size;
-    c.inside = c.dr > 0.0f && c.su >= 0.0f && c.su < sz && c.sv >= 0.0f && c.sv < sz;
-    return c;
-}
 
 __global__ __launch_bounds__(256) void k_hard(HardArgs a) {
     const int x = blockIdx.x * 64 + (threadIdx.x & 63);
@@ -147,9 +126,14 @@ __device__ __forceinline__ void pcss_items(const ShadowArgs& a, const float* bds
     }
 }
 
-// LDS: the disks are staged in LDS (at most kLdsSamples points each)
+// LDS: the disks are staged in LDS (at most kLdsSamples points each).  The
+// multi-resolution instance runs four waves per SIMD: its texels, near shadow
+// edges, search a large part of the map, which the L2 caches do not hold, and
+// more waves only make it worse (4K frame 230, 233 and 237 us at 4, 6 and 8;
+// 119 us with every tap in the same 16 KB).
 template <bool AL, bool LDS>
-__global__ __launch_bounds__(256) void k_pcss(ShadowArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(AL ? 4 : 1, AL ? 4 : 8)))
+void k_pcss(ShadowArgs a) {
     __shared__ float bds[LDS ? 2 * kLdsSamples : 1], pds[LDS ? 2 * kLdsSamples : 1];
     __shared__ float rows[kRowLevels * kRowTable];
     if (AL) stage_rows(a.c, rows);

@@ -356,6 +356,9 @@ struct FullresArgs {
 // launchers (return hipSuccess or the launch error)
 // ---------------------------------------------------------------------------
 hipError_t launch_edges(const EdgeArgs& a, int normal_dtype, hipStream_t s);
+// launch_edges with the shadow bits computed instead of read: at most 4
+// levels, width divisible by 4, bit-packed edges
+hipError_t launch_edges_shadow(const EdgeArgs& a, const HardArgs& ha, int normal_dtype, hipStream_t s);
 hipError_t launch_blur(const BlurArgs& a, hipStream_t s);       // levels with radius <= 8
 hipError_t launch_blur_wide(const BlurLevel& a, hipStream_t s);  // one level, radius 9..16
 constexpr int kBlurFusedMaxRadius = kBlurFusedMaxRadiusC;
