@@ -452,7 +452,7 @@ int do_build_masks(const mr_gbuffer* gb, const Geo& g, const mr_mask_params* mp,
             continue;
         }
         bl.tile_base = tiles;
-        tiles += bl.tiles_x * (unsigned)((bl.H + 31) / 32);
+        tiles += bl.tiles_x * (unsigned)((bl.H + kBlurTH - 1) / kBlurTH);
         ba.lv[ba.nlev++] = bl;
     }
     ba.ntiles = tiles;
@@ -470,8 +470,8 @@ int do_build_masks(const mr_gbuffer* gb, const Geo& g, const mr_mask_params* mp,
         NestArgs na{m->stencil[fi - 1], m->stencil[ci - 1], g.Wi[fi - 1], g.Hi[fi - 1], g.Wi[ci - 1], g.Hi[ci - 1], k};
         if (launch_nest(na, s) != hipSuccess) return fail(MR_E_DEVICE, "nesting kernel launch failed");
     }
+    LevelMapArgs la{};
     if (m->level_map) {
-        LevelMapArgs la{};
         la.nlev = g.nlev;
         for (int j = 0; j < g.nlev; ++j) {
             la.levels[j] = g.levels[j];
@@ -481,7 +481,6 @@ int do_build_masks(const mr_gbuffer* gb, const Geo& g, const mr_mask_params* mp,
         la.W = g.W;
         la.H = g.H;
         la.out = m->level_map;
-        if (launch_level_map(la, s) != hipSuccess) return fail(MR_E_DEVICE, "level map kernel launch failed");
     }
     CompactArgs ca{};
     ca.nlev = g.nlev - 1;
@@ -497,9 +496,8 @@ int do_build_masks(const mr_gbuffer* gb, const Geo& g, const mr_mask_params* mp,
     }
     ca.chunk_base[ca.nlev] = cb;
     ca.chunk_count = reinterpret_cast<uint32_t*>(base + sc.chunk_count_off);
-    ca.chunk_off = reinterpret_cast<uint32_t*>(base + sc.chunk_off_off);
     ca.count = m->count;
-    if (launch_compact(ca, s) != hipSuccess) return fail(MR_E_DEVICE, "compaction kernel launch failed");
+    if (launch_compact(ca, m->level_map ? &la : nullptr, s) != hipSuccess) return fail(MR_E_DEVICE, "compaction kernel launch failed");
     return MR_OK;
 }
 

@@ -2,13 +2,18 @@
 // lists of the texels to evaluate, in row-major ascending order, with the
 // list lengths left on the device.
 //
-// Three passes over the stencils of all compacted levels at once (a level's
+// Two launches over the stencils of all compacted levels at once (a level's
 // stencil is cut into chunks of 4096 texels, 16 per thread):
 //   count   - nonzero bytes per chunk (popcount of a byte mask, block sum);
-//   scan    - one workgroup turns chunk counts into chunk offsets per level
-//             and writes the level totals;
-//   scatter - each chunk recounts, takes a wave64 prefix sum of the per-thread
-//             counts plus the wave totals from LDS, and writes its indices.
+//             further blocks of the same launch write the owner-level map,
+//             which reads the same stencils;
+//   scatter - each chunk sums the counts of its level's earlier chunks (at
+//             most 65536 of them, 256 threads wide), recounts, takes a wave64
+//             prefix sum of the per-thread counts plus the wave totals from
+//             LDS, and writes its indices; a level's last chunk writes its
+//             total.
+// (The map, the count, a scan by one workgroup and the scatter were four
+// launches of 4 to 5 us each on a 1366 x 768 frame, most of it the launch.)
 #include "mr_internal.hpp"
 
 namespace mr {
@@ -42,9 +47,7 @@ __device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
     return v;
 }
 
-__global__ __launch_bounds__(256) void k_count(CompactArgs a) {
-    __shared__ unsigned wsum[4];
-    const unsigned c = blockIdx.x;
+__device__ __forceinline__ void count_chunk(const CompactArgs& a, unsigned c, unsigned* wsum) {
     const int l = find_level(a, c);
     const unsigned off = (c - a.chunk_base[l]) * kChunk + threadIdx.x * 16;
     unsigned cnt = 0;
@@ -59,38 +62,47 @@ __global__ __launch_bounds__(256) void k_count(CompactArgs a) {
     if (threadIdx.x == 0) a.chunk_count[c] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-__global__ __launch_bounds__(1024) void k_scan(CompactArgs a) {
-    __shared__ unsigned wtot[16];
-    const int t = threadIdx.x, lane = __lane_id(), wv = t >> 6;
-    // levels that are not compacted report 0
-    if (t < kMaxLevels) a.count[t] = 0;
-    __syncthreads();
-    for (int l = 0; l < a.nlev; ++l) {
-        const unsigned b0 = a.chunk_base[l], b1 = a.chunk_base[l + 1];
-        unsigned carry = 0;
-        for (unsigned base = b0; base < b1; base += 1024) {
-            const unsigned c = base + t;
-            const unsigned v = c < b1 ? a.chunk_count[c] : 0u;
-            const unsigned inc = wave_incl_scan(v);
-            if (lane == 63) wtot[wv] = inc;
-            __syncthreads();
-            unsigned before = 0, all = 0;
-            for (int w = 0; w < 16; ++w) {
-                if (w < wv) before += wtot[w];
-                all += wtot[w];
-            }
-            if (c < b1) a.chunk_off[c] = carry + before + inc - v;
-            carry += all;
-            __syncthreads();
+// owner-level map: the finest enabled level whose stencil covers the pixel;
+// a block writes kMapPixels consecutive pixels
+constexpr unsigned kMapPixels = 1024;
+__device__ __forceinline__ void map_chunk(const LevelMapArgs& a, unsigned c) {
+    const unsigned n = (unsigned)a.W * (unsigned)a.H;
+#pragma unroll
+    for (int q = 0; q < (int)(kMapPixels / 256u); ++q) {
+        const unsigned p = c * kMapPixels + 256u * q + threadIdx.x;
+        if (p >= n) return;
+        const unsigned y = p / (unsigned)a.W, x = p - y * (unsigned)a.W;
+        unsigned lvl = (unsigned)a.levels[a.nlev - 1];
+        for (int j = a.nlev - 2; j >= 0; --j) {
+            const int i = a.levels[j], sh = i - 1;
+            if (a.S[j][(y >> sh) * (unsigned)a.Wi[j] + (x >> sh)]) lvl = (unsigned)i;
         }
-        if (t == 0) a.count[a.count_idx[l]] = carry;
+        a.out[p] = (uint8_t)lvl;
     }
 }
 
-__global__ __launch_bounds__(256) void k_scatter(CompactArgs a) {
-    __shared__ unsigned wtot[4];
+// blocks 0 .. nchunks - 1 count, the others write the level map
+__global__ __launch_bounds__(256) void k_count_map(CompactArgs a, LevelMapArgs m, unsigned nchunks) {
+    __shared__ unsigned wsum[4];
+    if (blockIdx.x < nchunks)
+        count_chunk(a, blockIdx.x, wsum);
+    else
+        map_chunk(m, blockIdx.x - nchunks);
+}
+
+__global__ __launch_bounds__(256) void k_scatter(CompactArgs a, unsigned nchunks) {
+    __shared__ unsigned wtot[4], wpre[4];
     const unsigned c = blockIdx.x;
+    if (c == 0 && threadIdx.x < kMaxLevels) {  // levels that are not compacted report 0
+        bool listed = false;
+        for (int l = 0; l < a.nlev; ++l) listed = listed || a.count_idx[l] == (int)threadIdx.x;
+        if (!listed) a.count[threadIdx.x] = 0;
+    }
+    if (c >= nchunks) return;
     const int l = find_level(a, c);
+    unsigned pre = 0;  // entries of the level's earlier chunks
+    for (unsigned u = a.chunk_base[l] + threadIdx.x; u < c; u += 256) pre += a.chunk_count[u];
+    for (int d = 32; d >= 1; d >>= 1) pre += __shfl_xor(pre, d, 64);
     const unsigned base = (c - a.chunk_base[l]) * kChunk;
     const unsigned off = base + threadIdx.x * 16;
     uint4 v = make_uint4(0, 0, 0, 0);
@@ -101,11 +113,16 @@ __global__ __launch_bounds__(256) void k_scatter(CompactArgs a) {
     }
     const unsigned inc = wave_incl_scan(cnt);
     const int wv = threadIdx.x >> 6;
-    if (__lane_id() == 63) wtot[wv] = inc;
+    if (__lane_id() == 63) {
+        wtot[wv] = inc;
+        wpre[wv] = pre;
+    }
     __syncthreads();
-    unsigned before = 0;
+    unsigned before = wpre[0] + wpre[1] + wpre[2] + wpre[3];
+    if (threadIdx.x == 0 && c + 1u == a.chunk_base[l + 1])
+        a.count[a.count_idx[l]] = before + wtot[0] + wtot[1] + wtot[2] + wtot[3];
     for (int w = 0; w < wv; ++w) before += wtot[w];
-    unsigned pos = a.chunk_off[c] + before + inc - cnt;
+    unsigned pos = before + inc - cnt;
     if (!cnt) return;
     uint32_t* list = a.list[l];
     const unsigned words[4] = {v.x, v.y, v.z, v.w};
@@ -118,11 +135,13 @@ __global__ __launch_bounds__(256) void k_scatter(CompactArgs a) {
     }
 }
 
-hipError_t launch_compact(const CompactArgs& a, hipStream_t s) {
+hipError_t launch_compact(const CompactArgs& a, const LevelMapArgs* map, hipStream_t s) {
     const unsigned nchunks = a.chunk_base[a.nlev];
-    if (nchunks) hipLaunchKernelGGL(k_count, dim3(nchunks), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, a);
-    if (nchunks) hipLaunchKernelGGL(k_scatter, dim3(nchunks), dim3(256), 0, s, a);
+    unsigned maps = 0;
+    if (map) maps = ((unsigned)map->W * (unsigned)map->H + kMapPixels - 1u) / kMapPixels;
+    if (nchunks + maps)
+        hipLaunchKernelGGL(k_count_map, dim3(nchunks + maps), dim3(256), 0, s, a, map ? *map : LevelMapArgs{}, nchunks);
+    hipLaunchKernelGGL(k_scatter, dim3(nchunks ? nchunks : 1u), dim3(256), 0, s, a, nchunks);
     return hipGetLastError();
 }
 

@@ -1,7 +1,6 @@
 // Mask creation kernels: edge image with fused OR-downsampling (Sec. 3.1),
 // separable Gaussian blur with the Table 1 variances and stencil = mask > 0
-// (Sec. 3.1, Sec. 4.1), nesting of the inclusive levels and the owner-level
-// map.
+// (Sec. 3.1, Sec. 4.1) and nesting of the inclusive levels.
 #include "edges_tile.hpp"
 #include "mr_internal.hpp"
 
@@ -14,27 +13,15 @@ namespace mr {
 // then every thread classifies a 4 x 2 pixel block, ORs it to the level-2
 // texels in registers and the coarser levels through LDS.
 // ---------------------------------------------------------------------------
+// n (1..4) consecutive elements, widened; four at once whatever their
+// alignment (elements are at least element-aligned, which the vector loads of
+// this hardware accept)
 template <typename T>
-__device__ __forceinline__ void row4(const T* p, unsigned off, bool vec, int n, float* o);
-
-template <>
-__device__ __forceinline__ void row4<float>(const float* p, unsigned off, bool vec, int n, float* o) {
-    if (vec) {
-        const float4 v = *reinterpret_cast<const float4*>(p + off);
-        o[0] = v.x;
-        o[1] = v.y;
-        o[2] = v.z;
-        o[3] = v.w;
-    } else {
-        for (int k = 0; k < 4; ++k) o[k] = k < n ? p[off + k] : 0.0f;
-    }
-}
-
-template <>
-__device__ __forceinline__ void row4<_Float16>(const _Float16* p, unsigned off, bool vec, int n, float* o) {
-    if (vec) {
-        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-        const h4 v = *reinterpret_cast<const h4*>(p + off);
+__device__ __forceinline__ void row4(const T* p, unsigned off, int n, float* o) {
+    if (n == 4) {
+        typedef T t4 __attribute__((ext_vector_type(4)));
+        t4 v;
+        __builtin_memcpy(&v, p + off, sizeof(v));
         o[0] = (float)v.x;
         o[1] = (float)v.y;
         o[2] = (float)v.z;
@@ -66,7 +53,7 @@ __global__ __launch_bounds__(256) void k_edges_generic(EdgeArgs a, unsigned tile
     const bool has_hard = a.hard != nullptr;
     const bool any = xb < W && yb < H;
     const int ncol = min(4, W - xb);
-    const bool vec = ((W & 3) == 0) && ncol == 4;
+    const bool vec = ncol == 4;
 
     // ---- loads: rows yb-1 .. yb+2 (index 0..3), columns xb .. xb+3, and the
     // side columns xb-1 / xb+4 of rows yb, yb+1 ----
@@ -81,13 +68,14 @@ __global__ __launch_bounds__(256) void k_edges_generic(EdgeArgs a, unsigned tile
         uint8_t th[4] = {0, 0, 0, 0};
         if (rok) {
             const unsigned off = (unsigned)y * (unsigned)W + (unsigned)xb;
-            row4<float>(a.depth, off, vec, ncol, tz);
-            row4<NT>(nrm, off, vec, ncol, t0);
-            row4<NT>(nrm + plane, off, vec, ncol, t1);
-            row4<NT>(nrm + 2 * plane, off, vec, ncol, t2);
+            row4(a.depth, off, ncol, tz);
+            row4(nrm, off, ncol, t0);
+            row4(nrm + plane, off, ncol, t1);
+            row4(nrm + 2 * plane, off, ncol, t2);
             if (has_hard) {
                 if (vec) {
-                    const uchar4 v = *reinterpret_cast<const uchar4*>(a.hard + off);
+                    uchar4 v;
+                    __builtin_memcpy(&v, a.hard + off, sizeof(v));
                     th[0] = v.x;
                     th[1] = v.y;
                     th[2] = v.z;
@@ -178,9 +166,10 @@ __global__ __launch_bounds__(256) void k_edges_generic(EdgeArgs a, unsigned tile
             const int y = yb + r;
             if (y >= H) continue;
             const unsigned off = (unsigned)y * (unsigned)W + (unsigned)xb;
-            if (vec)
-                *reinterpret_cast<uchar4*>(a.E + off) = make_uchar4(e[r][0], e[r][1], e[r][2], e[r][3]);
-            else
+            if (vec) {
+                const uchar4 v = make_uchar4(e[r][0], e[r][1], e[r][2], e[r][3]);
+                __builtin_memcpy(a.E + off, &v, sizeof(v));
+            } else
                 for (int k = 0; k < ncol; ++k) a.E[off + k] = e[r][k];
         }
         // point-sampled level depth: z_i(X, Y) = z(s X + s/2, s Y + s/2)
@@ -362,113 +351,88 @@ hipError_t launch_edges(const EdgeArgs& a, int normal_dtype, hipStream_t s) {
 
 // ---------------------------------------------------------------------------
 // separable blur of every level below the coarsest in one launch.  A
-// workgroup owns 256 columns x 32 rows of one level: the edge bytes of the
-// tile plus its halo are staged in LDS in one batch, then each thread walks
-// down its column keeping the last 2r+1 horizontal sums in a register shift
-// ring, so every output needs one new horizontal sum.
+// workgroup owns 256 columns x kBlurTH rows of one level: the edge bytes of
+// the tile plus its halo become one bit each in LDS (a ballot per 64 bytes),
+// then each thread walks down its column keeping the last 2r+1 horizontal
+// sums in a register shift ring, so every output needs one new horizontal
+// sum, from a word of the row's bits.
 // h(x, y) = sum_k g[k] E(x + k, y) then a(x, y) = sum_k g[k] h(x, y + k), taps
 // in ascending k, accumulators from +0, zero outside the image; S = a > 0.
 // Terms with E = 0 contribute g * 0 = +0, so h adds g[k] exactly for the set
-// taps.
+// taps; a wave without edges in its rows writes zeros.
 // ---------------------------------------------------------------------------
-constexpr int kBlurTW = 256, kBlurTH = 32;
-constexpr int kBlurLW = kBlurTW + 2 * kMaxRadius;  // staged row stride (bytes)
+constexpr int kBlurTW = 256;
+constexpr int kBlurRowWords = (kBlurTW + 64) / 32;  // columns x0 - 32 .. x0 + 287
+constexpr int kBlurRows = kBlurTH + 2 * kMaxRadius;
 
 template <int R>
-__device__ __forceinline__ float hsum(const uint8_t* row, const float* g) {
+__device__ __forceinline__ float hsum(const unsigned* row, const float* g) {
+    constexpr int N = 2 * R + 1;
+    const unsigned first = threadIdx.x + 32u - R, w = first >> 5, sh = first & 31u;
+    unsigned m[2] = {__builtin_amdgcn_alignbit(row[w + 1], row[w], sh), 0u};
+    if (N > 32) m[1] = (row[w + 1] >> sh) & 1u;  // bit 32 of the window
+    if (N < 32) m[0] &= (1u << (N & 31)) - 1u;
+    if (__ballot((m[0] | m[1]) != 0u) == 0) return 0.0f;
     float acc = 0.0f;
 #pragma unroll
-    for (int k = 0; k <= 2 * R; ++k) acc = acc + g[k] * (row[k] ? 1.0f : 0.0f);
+    for (int k = 0; k < N; ++k)
+        acc = acc + __uint_as_float(__float_as_uint(g[k]) & (unsigned)__builtin_amdgcn_sbfe((int)m[k >> 5], k & 31, 1));
     return acc;
 }
 
 template <int R>
-__device__ __forceinline__ void blur_columns(const BlurLevel& a, const uint8_t* es, int x0, int y0) {
-    const int t = threadIdx.x;
-    const int X = x0 + t;
+__device__ __forceinline__ void blur_columns(const BlurLevel& a, const unsigned (*eb)[kBlurRowWords], int x0, int y0) {
+    const int X = x0 + (int)threadIdx.x;
     const int W = a.W, H = a.H;
     float g[2 * R + 1];
 #pragma unroll
     for (int k = 0; k <= 2 * R; ++k) g[k] = a.g[k];
-    // staged row yy holds image row y0 - R + yy, column t + k holds x0 - R + t + k
+    // staged row yy holds image row y0 - R + yy
     float ring[2 * R + 1];
     ring[0] = 0.0f;
 #pragma unroll
-    for (int yy = 0; yy < 2 * R; ++yy) ring[yy + 1] = hsum<R>(es + yy * kBlurLW + t, g);
+    for (int yy = 0; yy < 2 * R; ++yy) ring[yy + 1] = hsum<R>(eb[yy], g);
     const bool colok = X < W;
     const int rows = min(kBlurTH, H - y0);
     for (int oy = 0; oy < rows; ++oy) {
 #pragma unroll
         for (int k = 0; k < 2 * R; ++k) ring[k] = ring[k + 1];
-        ring[2 * R] = hsum<R>(es + (oy + 2 * R) * kBlurLW + t, g);
+        ring[2 * R] = hsum<R>(eb[oy + 2 * R], g);
         float acc = 0.0f;
 #pragma unroll
         for (int k = 0; k <= 2 * R; ++k) acc = acc + g[k] * ring[k];
         if (colok) {
-            const long long p = (long long)(y0 + oy) * W + X;
+            const unsigned p = (unsigned)(y0 + oy) * (unsigned)W + (unsigned)X;
             a.a[p] = acc;
             a.S[p] = acc > 0.0f ? 1 : 0;
         }
     }
 }
 
-// Stage the tile's edge bytes (rows y0 - r .. y0 + 31 + r, columns
-// x0 - r .. x0 + 255 + r) into LDS with all global loads issued first.
-__device__ __forceinline__ void blur_stage(const BlurLevel& a, uint8_t* es, int x0, int y0) {
-    const int r = a.r, W = a.W, H = a.H, t = threadIdx.x;
-    const int eh = kBlurTH + 2 * r;
-    const bool vec = (W & 3) == 0;
-    constexpr int kWords = kBlurTW / 4;
-    constexpr int kMaxSlots = ((kBlurTH + 2 * kMaxRadius) * kWords + 255) / 256;
-    uchar4 v[kMaxSlots];
+// The tile's edges as bits in LDS: rows y0 - r .. y0 + kBlurTH - 1 + r,
+// columns x0 - 32 .. x0 + 287, 0 outside the image; the loads of kLoads
+// wave-wide pieces are in flight together.
+__device__ __forceinline__ void blur_stage(const BlurLevel& a, unsigned (*eb)[kBlurRowWords], int x0, int y0) {
+    constexpr int kPieces = kBlurRowWords / 2, kLoads = 8;  // pieces of 64 columns per row
+    const int W = a.W, H = a.H, lane = (int)__lane_id(), wave = (int)threadIdx.x >> 6;
+    const int n = (kBlurTH + 2 * a.r) * kPieces;
+    const __amdgpu_buffer_rsrc_t re = buf_rsrc(a.Ei, (unsigned)W * (unsigned)H);
+    for (int i0 = wave; i0 < n; i0 += 4 * kLoads) {
+        unsigned v[kLoads];
 #pragma unroll
-    for (int j = 0; j < kMaxSlots; ++j) {
-        const int idx = t + 256 * j;
-        const int yy = idx / kWords, q = idx % kWords;
-        const int Y = y0 - r + yy, X = x0 + 4 * q;
-        v[j] = make_uchar4(0, 0, 0, 0);
-        if (yy < eh && Y >= 0 && Y < H && X < W) {
-            const long long p = (long long)Y * W + X;
-            if (vec) {
-                v[j] = *reinterpret_cast<const uchar4*>(a.Ei + p);
-            } else {
-                uint8_t e4[4] = {0, 0, 0, 0};
-                for (int k = 0; k < 4 && X + k < W; ++k) e4[k] = a.Ei[p + k];
-                v[j] = make_uchar4(e4[0], e4[1], e4[2], e4[3]);
-            }
+        for (int j = 0; j < kLoads; ++j) {
+            const int i = i0 + 4 * j, yy = i / kPieces, q = i - yy * kPieces;
+            const int Y = y0 - a.r + yy, X = x0 - 32 + 64 * q + lane;
+            const bool in = i < n && (unsigned)Y < (unsigned)H && (unsigned)X < (unsigned)W;
+            // past the end a load returns 0
+            v[j] = __builtin_amdgcn_raw_buffer_load_b8(re, in ? (unsigned)Y * (unsigned)W + (unsigned)X : 0xFFFFFFFFu, 0, 0);
         }
-    }
-    // side halos: r columns on each side, at most (32 + 2*16) * 2*16 = 2048 bytes
-    constexpr int kHaloSlots = (kBlurTH + 2 * kMaxRadius) * 2 * kMaxRadius / 256;
-    uint8_t hb[kHaloSlots];
 #pragma unroll
-    for (int j = 0; j < kHaloSlots; ++j) {
-        hb[j] = 0;
-        const int idx = t + 256 * j;
-        if (idx >= eh * 2 * r) continue;
-        const int yy = idx / (2 * r), jj = idx % (2 * r);
-        const int xx = jj < r ? jj : kBlurTW + jj;
-        const int X = x0 - r + xx, Y = y0 - r + yy;
-        if (X >= 0 && X < W && Y >= 0 && Y < H) hb[j] = a.Ei[(long long)Y * W + X];
-    }
-#pragma unroll
-    for (int j = 0; j < kMaxSlots; ++j) {
-        const int idx = t + 256 * j;
-        const int yy = idx / kWords, q = idx % kWords;
-        if (yy >= eh) continue;
-        uint8_t* d = es + yy * kBlurLW + r + 4 * q;
-        d[0] = v[j].x;
-        d[1] = v[j].y;
-        d[2] = v[j].z;
-        d[3] = v[j].w;
-    }
-#pragma unroll
-    for (int j = 0; j < kHaloSlots; ++j) {
-        const int idx = t + 256 * j;
-        if (idx >= eh * 2 * r) continue;
-        const int yy = idx / (2 * r), jj = idx % (2 * r);
-        const int xx = jj < r ? jj : kBlurTW + jj;
-        es[yy * kBlurLW + xx] = hb[j];
+        for (int j = 0; j < kLoads; ++j) {
+            const int i = i0 + 4 * j, yy = i / kPieces, q = i - yy * kPieces;
+            const unsigned long long bits = __ballot(v[j] != 0u);
+            if (i < n && lane < 2) eb[yy][2 * q + lane] = lane ? (unsigned)(bits >> 32) : (unsigned)bits;
+        }
     }
     __syncthreads();
 }
@@ -477,7 +441,7 @@ __device__ __forceinline__ void blur_stage(const BlurLevel& a, uint8_t* es, int 
 // levels share one index range; the plain block order spreads the costlier
 // coarse-level tiles over all XCDs.
 __global__ __launch_bounds__(256) void k_blur(BlurArgs A) {
-    __shared__ uint8_t es[(kBlurTH + 2 * kMaxRadius) * kBlurLW];
+    __shared__ unsigned eb[kBlurRows][kBlurRowWords];
     const unsigned b = blockIdx.x;
     int l = 0;
     while (l + 1 < A.nlev && b >= A.lv[l + 1].tile_base) ++l;
@@ -485,11 +449,11 @@ __global__ __launch_bounds__(256) void k_blur(BlurArgs A) {
     const unsigned tile = b - a.tile_base;
     const int x0 = (int)(tile % a.tiles_x) * kBlurTW;
     const int y0 = (int)(tile / a.tiles_x) * kBlurTH;
-    blur_stage(a, es, x0, y0);
+    blur_stage(a, eb, x0, y0);
     const int r = a.r;
     switch (r) {
 #define MR_BLUR_CASE(R) \
-    case R: blur_columns<R>(a, es, x0, y0); break;
+    case R: blur_columns<R>(a, eb, x0, y0); break;
         MR_BLUR_CASE(0) MR_BLUR_CASE(1) MR_BLUR_CASE(2) MR_BLUR_CASE(3) MR_BLUR_CASE(4) MR_BLUR_CASE(5)
         MR_BLUR_CASE(6) MR_BLUR_CASE(7) MR_BLUR_CASE(8)
 #undef MR_BLUR_CASE
@@ -500,12 +464,12 @@ __global__ __launch_bounds__(256) void k_blur(BlurArgs A) {
 // radius 9..16: one launch per level, radius fixed at compile time
 template <int R>
 __global__ __launch_bounds__(256) void k_blur_wide(BlurLevel a) {
-    __shared__ uint8_t es[(kBlurTH + 2 * kMaxRadius) * kBlurLW];
+    __shared__ unsigned eb[kBlurRows][kBlurRowWords];
     const unsigned tile = xcd_remap(blockIdx.x, gridDim.x);
     const int x0 = (int)(tile % a.tiles_x) * kBlurTW;
     const int y0 = (int)(tile / a.tiles_x) * kBlurTH;
-    blur_stage(a, es, x0, y0);
-    blur_columns<R>(a, es, x0, y0);
+    blur_stage(a, eb, x0, y0);
+    blur_columns<R>(a, eb, x0, y0);
 }
 
 hipError_t launch_blur_wide(const BlurLevel& a, hipStream_t s) {
@@ -544,29 +508,6 @@ __global__ __launch_bounds__(256) void k_nest(NestArgs a) {
 hipError_t launch_nest(const NestArgs& a, hipStream_t s) {
     const long long n = (long long)a.Wc * a.Hc;
     hipLaunchKernelGGL(k_nest, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// owner-level map: finest enabled level whose stencil covers the pixel
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_level_map(LevelMapArgs a) {
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= a.W || y >= a.H) return;
-    uint8_t lvl = (uint8_t)a.levels[a.nlev - 1];
-    for (int j = 0; j < a.nlev - 1; ++j) {
-        const int i = a.levels[j], sh = i - 1;
-        if (a.S[j][(long long)(y >> sh) * a.Wi[j] + (x >> sh)]) {
-            lvl = (uint8_t)i;
-            break;
-        }
-    }
-    a.out[(long long)y * a.W + x] = lvl;
-}
-
-hipError_t launch_level_map(const LevelMapArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_level_map, dim3((a.W + 63) / 64, (a.H + 3) / 4), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -12,6 +12,7 @@ namespace mr {
 constexpr int kMaxLevels = MR_MAX_LEVELS;
 constexpr int kBlurFusedMaxRadiusC = 8;  // largest radius of the single-launch blur and the lean path
 constexpr int kMaxRadius = MR_MAX_RADIUS;
+constexpr int kBlurTH = 8;       // rows of a blur tile
 constexpr int kChunk = 4096;  // texels per compaction chunk (256 threads x 16)
 
 // ---------------------------------------------------------------------------
@@ -135,7 +136,6 @@ struct CompactArgs {
     int count_idx[kMaxLevels];       // index into count[] per compacted level
     int nlev;                        // compacted levels
     uint32_t* chunk_count;           // [total chunks]
-    uint32_t* chunk_off;             // [total chunks]
     uint32_t* count;                 // [MR_MAX_LEVELS]
 };
 
@@ -363,8 +363,8 @@ hipError_t launch_blur(const BlurArgs& a, hipStream_t s);       // levels with r
 hipError_t launch_blur_wide(const BlurLevel& a, hipStream_t s);  // one level, radius 9..16
 constexpr int kBlurFusedMaxRadius = kBlurFusedMaxRadiusC;
 hipError_t launch_nest(const NestArgs& a, hipStream_t s);
-hipError_t launch_level_map(const LevelMapArgs& a, hipStream_t s);
-hipError_t launch_compact(const CompactArgs& a, hipStream_t s);
+// map: the owner-level map to write too (null: none)
+hipError_t launch_compact(const CompactArgs& a, const LevelMapArgs* map, hipStream_t s);
 hipError_t launch_ssao(const SsaoArgs& a, int normal_dtype, unsigned total_hint, hipStream_t s);
 hipError_t launch_hard(const HardArgs& a, hipStream_t s);
 hipError_t launch_shadow(const ShadowArgs& a, unsigned total_hint, hipStream_t s);
