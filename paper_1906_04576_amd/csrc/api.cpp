@@ -230,7 +230,7 @@ int check_sampling(const float* kernel, int S, float r, float b) {
 // ---------------------------------------------------------------------------
 struct MaskScratch {
     size_t Ei_off[kMaxLevels] = {};
-    size_t chunk_count_off = 0, chunk_off_off = 0;
+    size_t chunk_count_off = 0;
     unsigned nchunks = 0;
     size_t bytes = 0;
 };
@@ -246,8 +246,6 @@ MaskScratch mask_scratch(const Geo& g) {
     }
     for (int j = 0; j + 1 < g.nlev; ++j) s.nchunks += (unsigned)((g.n(g.levels[j]) + kChunk - 1) / kChunk);
     s.chunk_count_off = off;
-    off += align256((size_t)s.nchunks * 4 + 4);
-    s.chunk_off_off = off;
     off += align256((size_t)s.nchunks * 4 + 4);
     s.bytes = off;
     return s;

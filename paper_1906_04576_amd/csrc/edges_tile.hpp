@@ -25,8 +25,8 @@ __device__ __forceinline__ bool ndot_lt(const float* a, const float* b, float cn
 
 
 // ---------------------------------------------------------------------------
-// Fast path for W divisible by 4 (every image with N >= 3 levels): the same
-// classification, branch-free, with buffer loads (descriptor + 32-bit offset)
+// Fast path for W divisible by 4 (every image with N >= 3 levels), and RAG
+// for other widths of at least 4: the same classification, branch-free, with buffer loads (descriptor + 32-bit offset)
 // of clamped rows and columns.  Rows or columns outside the image are loaded
 // from a clamped position and only ever used behind the border flags.
 // ---------------------------------------------------------------------------
@@ -228,9 +228,24 @@ __device__ __forceinline__ void edges_hard(const HardArgs& ha, const EdgeGeom& g
         }
 }
 
+// v[0..3] <- the last 4 - d values, for a lane whose four columns were loaded
+// d columns to the left
+template <typename T>
+__device__ __forceinline__ void shift_columns(T (&v)[4], int d) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        const bool m = d > s;
+        v[0] = m ? v[1] : v[0];
+        v[1] = m ? v[2] : v[1];
+        v[2] = m ? v[3] : v[2];
+    }
+}
+
 // One tile of the edge image from its loads; tile k also zeroes counter
-// words 256 k .. 256 k + 255 (those below zero_n).
-template <typename NT, bool HARD, bool BITS, bool WIDE>
+// words 256 k .. 256 k + 255 (those below zero_n).  RAG: the width need not
+// be divisible by 4 (so at most 2 levels): the last lane of a row has fewer
+// than four pixels and loaded the row's last four columns.
+template <typename NT, bool HARD, bool BITS, bool WIDE, bool RAG = false>
 __device__ __forceinline__ void edges_process(const EdgeArgs& a, const EdgeGeom& g, unsigned tile,
                                               const EdgeLoads<NT, HARD>& L) {
     typedef NormalRow<NT> NR;
@@ -275,6 +290,34 @@ __device__ __forceinline__ void edges_process(const EdgeArgs& a, const EdgeGeom&
             for (int c = 0; c < 3; ++c) hn[k][c] = t3[c][k];
     }
     const unsigned hh = L.hh;
+    float hz_[4] = {hz[0], hz[1], hz[2], hz[3]};
+    if constexpr (RAG) {
+        const int d = any ? xb - g.xc : 0;
+        if (__ballot(d != 0) != 0) {
+            shift_columns(hz_, d);
+            float t4[4];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) t4[k] = hn[k][c];
+                shift_columns(t4, d);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) hn[k][c] = t4[k];
+            }
+#pragma unroll
+            for (int r = 1; r <= 2; ++r) {
+                shift_columns(z[r], d);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) t4[k] = n[r][k][c];
+                    shift_columns(t4, d);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) n[r][k][c] = t4[k];
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
@@ -288,8 +331,8 @@ __device__ __forceinline__ void edges_process(const EdgeArgs& a, const EdgeGeom&
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const float za = __shfl(z[2][k], lup, 64), zb = __shfl(z[1][k], ldn, 64);
-        z[0][k] = top ? hz[k] : za;
-        z[3][k] = bot ? hz[k] : zb;
+        z[0][k] = top ? hz_[k] : za;
+        z[3][k] = bot ? hz_[k] : zb;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const float na = __shfl(n[2][k][c], lup, 64), nb_ = __shfl(n[1][k][c], ldn, 64);
@@ -398,7 +441,7 @@ __device__ __forceinline__ void edges_process(const EdgeArgs& a, const EdgeGeom&
                 const unsigned hu_ = (hrow[r] >> sh) & 0xFFu, hd_ = (hrow[r + 2] >> sh) & 0xFFu;
                 ed |= (hl & (hl_ != hc)) | (hr & (hr_ != hc)) | (hu & (hu_ != hc)) | (hd & (hd_ != hc));
             }
-            e[r][c] = (any & (y < H) & fovea(a, x, y, valid_depth(zc) & ed)) ? 1 : 0;
+            e[r][c] = (any & (y < H) & (!RAG || x < W) & fovea(a, x, y, valid_depth(zc) & ed)) ? 1 : 0;
         }
     }
     if (BITS) {
@@ -428,9 +471,16 @@ __device__ __forceinline__ void edges_process(const EdgeArgs& a, const EdgeGeom&
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             const int y = yb + r;
-            if (y < H)
-                *reinterpret_cast<uchar4*>(a.E + (unsigned)y * (unsigned)W + (unsigned)xb) =
-                    make_uchar4(e[r][0], e[r][1], e[r][2], e[r][3]);
+            if (y >= H) continue;
+            uint8_t* p = a.E + (unsigned)y * (unsigned)W + (unsigned)xb;
+            if (RAG && xb + 4 > W) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (xb + k < W) p[k] = e[r][k];
+            } else {
+                const uchar4 v = make_uchar4(e[r][0], e[r][1], e[r][2], e[r][3]);
+                __builtin_memcpy(p, &v, sizeof(v));
+            }
         }
     }
     if (any) {
@@ -440,7 +490,7 @@ __device__ __forceinline__ void edges_process(const EdgeArgs& a, const EdgeGeom&
         if (a.zi[1]) {
             float* z2 = a.zi[1] + (unsigned)(yb >> 1) * (unsigned)a.Wi[1] + (unsigned)(xb >> 1);
             z2[0] = z[2][1];
-            z2[1] = z[2][3];
+            if (!RAG || xb + 2 < W) z2[1] = z[2][3];
         }
         for (int i = 3; i <= a.num_levels; ++i) {
             float* zi = a.zi[i - 1];
@@ -454,7 +504,7 @@ __device__ __forceinline__ void edges_process(const EdgeArgs& a, const EdgeGeom&
         if (!BITS && a.Ei[1]) {
             uint8_t* e2 = a.Ei[1] + (unsigned)(yb >> 1) * (unsigned)a.Wi[1] + (unsigned)(xb >> 1);
             e2[0] = e[0][0] | e[0][1] | e[1][0] | e[1][1];
-            e2[1] = e[0][2] | e[0][3] | e[1][2] | e[1][3];
+            if (!RAG || xb + 2 < W) e2[1] = e[0][2] | e[0][3] | e[1][2] | e[1][3];
         }
     }
     int v = e[0][0] | e[0][1] | e[0][2] | e[0][3] | e[1][0] | e[1][1] | e[1][2] | e[1][3];
@@ -497,12 +547,12 @@ __device__ __forceinline__ void edges_process(const EdgeArgs& a, const EdgeGeom&
 }
 
 // One tile of the edge image: its loads, then the classification.
-template <typename NT, bool HARD, bool BITS, bool WIDE>
+template <typename NT, bool HARD, bool BITS, bool WIDE, bool RAG = false>
 __device__ __forceinline__ void edges_tile(const EdgeArgs& a, unsigned tile, unsigned tiles_x) {
     const EdgeGeom g = edge_geom<WIDE>(a, tile, tiles_x);
     EdgeLoads<NT, HARD> L;
     edges_load<NT, HARD, WIDE>(a, g, L);
-    edges_process<NT, HARD, BITS, WIDE>(a, g, tile, L);
+    edges_process<NT, HARD, BITS, WIDE, RAG>(a, g, tile, L);
 }
 
 }  // namespace mr

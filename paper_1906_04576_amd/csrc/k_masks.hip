@@ -233,6 +233,13 @@ __global__ __launch_bounds__(256) void k_edges_vec(EdgeArgs a, unsigned tiles_x,
     edges_tile<NT, HARD, BITS, WIDE>(a, xcd_remap(blockIdx.x, ntiles), tiles_x);
 }
 
+// Widths not divisible by 4 (at most 2 levels), no shadow bits.  Rows start
+// on any element, so the four-pixel loads are aligned to elements only.
+template <typename NT>
+__global__ __launch_bounds__(256) void k_edges_ragged(EdgeArgs a, unsigned tiles_x, unsigned ntiles) {
+    edges_tile<NT, false, false, true, true>(a, xcd_remap(blockIdx.x, ntiles), tiles_x);
+}
+
 // The edge image of a soft-shadow frame with the one-sample shadow test of
 // its pixels in the same tile: the depth is read once, and the shadow bits of
 // a 3840 x 2160 frame (a 33 MB read and 8 MB written, then read again) are
@@ -341,6 +348,15 @@ hipError_t launch_edges(const EdgeArgs& a, int normal_dtype, hipStream_t s) {
             else MR_EDGES(float, false, false);
         }
 #undef MR_EDGES
+    } else if (a.W >= 4 && !hard && a.num_levels <= 2 && (!f16 || (a.W & 1) == 0)) {
+        // (half normals of an odd width would need loads aligned to 2 bytes;
+        // shadow bits, loads aligned to 1)
+        unsigned wx, wn;
+        edges_tiles(a.W, a.H, true, wx, wn);
+        if (f16)
+            hipLaunchKernelGGL(k_edges_ragged<_Float16>, dim3(wn), dim3(256), 0, s, a, wx, wn);
+        else
+            hipLaunchKernelGGL(k_edges_ragged<float>, dim3(wn), dim3(256), 0, s, a, wx, wn);
     } else if (f16) {
         hipLaunchKernelGGL(k_edges_generic<_Float16>, dim3(n), dim3(256), 0, s, a, tx, n);
     } else {
