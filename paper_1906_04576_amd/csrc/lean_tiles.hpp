@@ -624,42 +624,66 @@ __device__ __forceinline__ void blend4(const float* la, const float (*lc)[Region
     }
 }
 
-// one staged texel: index k of the (kMergeTW >> SH) + 2 columns wide region
-// of the level in argument slot LV (scale 2^SH) around the tile at (x0, y0),
-// clamped to the level; DENSE: the coarsest level, read densely, the others
-// by rank (a = 0 and values 0 off the stencil)
-template <int LV, int SH, int RW, int C, typename VT, bool DENSE = LV == 3>
-__device__ __forceinline__ void stage4(const LeanMergeArgs& a, int k, int x0, int y0, float& av, float (&cv)[C]) {
-    const LeanMergeLevel& L = a.lv[LV];
+// value k of a sub-image plane (f32 or f16 storage) through its buffer; 0 at kNoRank
+constexpr unsigned kNoRank = 0x3FFFFFFFu;
+template <typename VT>
+__device__ __forceinline__ float buf_val(__amdgpu_buffer_rsrc_t r, unsigned k) {
+    if constexpr (sizeof(VT) == 4)
+        return buf_f1(r, k * 4u);
+    else
+        return (float)__builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, (int)(k * 2u), 0, 0));
+}
+
+// Level texel of index k in the region of scale 2^SH staged for the tile at
+// (x0, y0), clamped to the level: always inside it, for every k >= 0.
+template <int SH>
+__device__ __forceinline__ void region_texel(const LeanMergeLevel& L, int k, int x0, int y0, int& X, int& Y) {
+    constexpr int RW = Region4<SH>::rw;
     const int yy = k / RW, xx = k - yy * RW;
-    const int Xl = min(max((x0 >> SH) - 1 + xx, 0), L.W - 1);
-    const int Yl = min(max((y0 >> SH) - 1 + yy, 0), L.H - 1);
-    av = 0.0f;
-#pragma unroll
-    for (int c = 0; c < C; ++c) cv[c] = 0.0f;
-    if (DENSE) {
-        const unsigned p = (unsigned)Yl * (unsigned)L.W + (unsigned)Xl;
-#pragma unroll
-        for (int c = 0; c < C; ++c) cv[c] = cval<VT>(L.c, c * L.c_plane + p);
-    } else {
-        const unsigned wi = (unsigned)Yl * (unsigned)L.wpr + (unsigned)(Xl >> 5);
-        const unsigned word = L.Sb[wi];
-        const unsigned bit = (unsigned)Xl & 31u;
-        if ((word >> bit) & 1u) {
-            const unsigned rank = L.woff[wi] + __popc(word & ((1u << bit) - 1u));
-            av = L.ac[rank];
-#pragma unroll
-            for (int c = 0; c < C; ++c) cv[c] = cval<VT>(L.c, c * L.c_plane + rank);
-        }
-    }
+    X = min(max((x0 >> SH) - 1 + xx, 0), L.W - 1);
+    Y = min(max((y0 >> SH) - 1 + yy, 0), L.H - 1);
+}
+
+// the stencil word that holds texel (X, Y) of a list level, and the rank of
+// the word's first texel
+struct RankWord {
+    unsigned word, off, bit;
+};
+
+__device__ __forceinline__ RankWord rank_word(const LeanMergeLevel& L, int X, int Y) {
+    const unsigned wi = (unsigned)Y * (unsigned)L.wpr + (unsigned)(X >> 5);
+    return {L.Sb[wi], L.woff[wi], (unsigned)X & 31u};
+}
+
+__device__ __forceinline__ unsigned rank_of(const RankWord& w) {
+    return w.off + __popc(w.word & ((1u << w.bit) - 1u));
 }
 
 template <int C>
 struct Merge4Lds {
     float la2[Region4<1>::n], la3[Region4<2>::n];
     float lc2[C][Region4<1>::n], lc3[C][Region4<2>::n], lc4[C][Region4<3>::n];
-    int any2, any3;
+    alignas(4) uint8_t any2[4];
+    alignas(4) uint8_t any3[4];  // per wave: it staged some a > 0
 };
+
+// a and the values of the texel that w points to, 0 where it is off the
+// stencil (or not wanted): such lanes read past the buffers' ends
+template <int C, typename VT>
+__device__ __forceinline__ void rank_values(const LeanMergeLevel& L, const RankWord& w, bool want, float& av,
+                                            float (&cv)[C]) {
+    const bool in = want && ((w.word >> w.bit) & 1u);
+    av = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) cv[c] = 0.0f;
+    if (!__ballot(in)) return;
+    const unsigned n = (unsigned)L.W * (unsigned)L.H;
+    const unsigned k = in ? rank_of(w) : kNoRank;
+    av = buf_val<float>(buf_rsrc(L.ac, n * 4u), k);
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+        cv[c] = buf_val<VT>(buf_rsrc(static_cast<const VT*>(L.c) + c * L.c_plane, n * (unsigned)sizeof(VT)), k);
+}
 
 // L2 false: the levels 1, 3 and 4 (SSGI's Table 1 column), in argument
 // slots 0, 1 and 2: the same merge without level 2's staging and blend.
@@ -675,33 +699,36 @@ __device__ __forceinline__ void merge4_tile(const LeanMergeArgs& a, unsigned til
     float (*lc2)[R2::n] = sm.lc2;
     float (*lc3)[R3::n] = sm.lc3;
     float (*lc4)[R4::n] = sm.lc4;
-    int& any2 = sm.any2;
-    int& any3 = sm.any3;
     const int x0 = (int)(tile % tiles_x) * kMergeTW;
     const int y0 = (int)(tile / tiles_x) * kMergeTH;
     const int t = threadIdx.x;
-    if (t == 0) any2 = any3 = 0;
-    __syncthreads();
     // ---- stage levels 2, 3 (by rank, 0 off the stencil) and 4 (dense) ----
-    // Every thread stages texel t of level 2 and at most one more: level 2's
-    // remaining texels on threads [0, nB), level 4 on [nB, nB + n4), level 3
-    // on [128, 128 + n3).  Each slot's level is fixed at compile time, so its
-    // parameters are scalar and its divisions by the region width constant.
-    // Without level 2: level 4 on threads [0, n4), level 3 on [128, 128 + n3).
+    // Every thread stages texel t of level 2 and at most one more by rank:
+    // waves 0 and 1 level 2's remaining texels, waves 2 and 3 level 3; level
+    // 4 is staged by the threads from n4lo on.  A block's time is its chain
+    // of dependent loads, so these come in two phases: the stencil words and
+    // word ranks of all slots and of the thread's own pixels, then all
+    // values.  (Word, rank and value one after another in a branch for each
+    // slot: one channel at 4K 21.6 us, now 20.1 us; eight frames of three
+    // channels in a batch 147 us, now 135 us.  The rest is the blends' ~300
+    // instructions per wave and the image's store.)
     constexpr int nB = R2::n - 256;
     constexpr int n4lo = L2 ? nB : 0;  // first thread staging level 4
     static_assert(nB > 0 && nB + R4::n <= 128 && 128 + R3::n <= 256, "merge staging layout");
-    float av[2], cv[2][C];
-    av[0] = av[1] = 0.0f;
-#pragma unroll
-    for (int c = 0; c < C; ++c) cv[0][c] = cv[1][c] = 0.0f;
-    if constexpr (L2) stage4<1, 1, R2::rw, C, VT>(a, t, x0, y0, av[0], cv[0]);
-    if (L2 && t < nB)
-        stage4<1, 1, R2::rw, C, VT>(a, 256 + t, x0, y0, av[1], cv[1]);
-    else if (t >= n4lo && t < n4lo + R4::n)
-        stage4<I4, 3, R4::rw, C, VT, true>(a, t - n4lo, x0, y0, av[1], cv[1]);
-    else if (t >= 128 && t < 128 + R3::n)
-        stage4<I3, 2, R3::rw, C, VT, false>(a, t - 128, x0, y0, av[1], cv[1]);
+    const bool lower = __builtin_amdgcn_readfirstlane(t) < 128;  // wave 0 or 1
+    const LeanMergeLevel& LS = a.lv[L2 && lower ? 1 : I3];  // level of the second slot
+    const bool want1 = lower ? L2 && t < nB : t < 128 + R3::n;
+    int X, Y_;
+    RankWord w0 = {0, 0, 0};
+    if constexpr (L2) {
+        region_texel<1>(a.lv[1], t, x0, y0, X, Y_);
+        w0 = rank_word(a.lv[1], X, Y_);
+    }
+    if (lower)
+        region_texel<1>(LS, 256 + t, x0, y0, X, Y_);
+    else
+        region_texel<2>(LS, t - 128, x0, y0, X, Y_);
+    RankWord w1 = rank_word(LS, L2 || !lower ? X : 0, L2 || !lower ? Y_ : 0);
     // a wave covers a 16 x 16 pixel square of the tile (four pixels of a row
     // per thread), so that the pixels near a stencil, where the blends run,
     // fill fewer waves
@@ -709,29 +736,42 @@ __device__ __forceinline__ void merge4_tile(const LeanMergeArgs& a, unsigned til
     const int Y = y0 + (l >> 2);
     const int XQ = x0 + 16 * w + 4 * (l & 3);
     const bool active = Y < a.H && XQ < a.W;
-    // ---- level 1: four pixels per thread, values by rank ----
+    // level 1: four pixels per thread, values by rank
+    const RankWord wp = rank_word(a.lv[0], min(XQ, a.W - 4), min(Y, a.H - 1));
+    float cv4[C];
+    const bool own4 = t >= n4lo && t < n4lo + R4::n;
+    {
+        const LeanMergeLevel& L = a.lv[I4];
+        region_texel<3>(L, own4 ? t - n4lo : 0, x0, y0, X, Y_);
+        const unsigned n = (unsigned)L.W * (unsigned)L.H;
+        const unsigned p = own4 ? (unsigned)Y_ * (unsigned)L.W + (unsigned)X : kNoRank;
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            cv4[c] = buf_val<VT>(buf_rsrc(static_cast<const VT*>(L.c) + c * L.c_plane, n * (unsigned)sizeof(VT)), p);
+    }
+    float av[2], cv[2][C];
+    if constexpr (L2) rank_values<C, VT>(a.lv[1], w0, true, av[0], cv[0]);
+    rank_values<C, VT>(LS, w1, want1, av[1], cv[1]);
     float a1[4] = {0, 0, 0, 0}, c1[C][4];
-    unsigned nib = 0;
 #pragma unroll
     for (int c = 0; c < C; ++c) c1[c][0] = c1[c][1] = c1[c][2] = c1[c][3] = 0.0f;
-    if (active) {
+    const unsigned nib = active ? (wp.word >> wp.bit) & 0xFu : 0u;
+    if (__ballot(nib != 0)) {
         const LeanMergeLevel& L = a.lv[0];
-        const unsigned wi = (unsigned)Y * (unsigned)L.wpr + (unsigned)(XQ >> 5);
-        const unsigned word = L.Sb[wi];
-        const unsigned bit = (unsigned)XQ & 31u;
-        nib = (word >> bit) & 0xFu;
-        if (nib) {
-            unsigned rank = L.woff[wi] + __popc(word & ((1u << bit) - 1u));
+        const unsigned n = (unsigned)L.W * (unsigned)L.H;
+        const unsigned rank = rank_of(wp);
+        unsigned k1[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if ((nib >> k) & 1u) {
-                    a1[k] = L.ac[rank];
+        for (int k = 0; k < 4; ++k)
+            k1[k] = (nib >> k) & 1u ? rank + __popc(nib & ((1u << k) - 1u)) : kNoRank;
 #pragma unroll
-                    for (int c = 0; c < C; ++c) c1[c][k] = cval<VT>(L.c, c * L.c_plane + rank);
-                    ++rank;
-                }
-            }
-        }
+        for (int k = 0; k < 4; ++k) a1[k] = buf_val<float>(buf_rsrc(L.ac, n * 4u), k1[k]);
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                c1[c][k] = buf_val<VT>(
+                    buf_rsrc(static_cast<const VT*>(L.c) + c * L.c_plane, n * (unsigned)sizeof(VT)), k1[k]);
     }
     bool nz2 = false, nz3 = false;
     if constexpr (L2) {
@@ -740,24 +780,29 @@ __device__ __forceinline__ void merge4_tile(const LeanMergeArgs& a, unsigned til
         for (int c = 0; c < C; ++c) lc2[c][t] = cv[0][c];
         nz2 = av[0] != 0.0f;
     }
-    if (L2 && t < nB) {
-        la2[256 + t] = av[1];
+    if (want1) {
+        float* la = L2 && lower ? la2 + 256 + t : la3 + (t - 128);
+        *la = av[1];
 #pragma unroll
-        for (int c = 0; c < C; ++c) lc2[c][256 + t] = cv[1][c];
-        nz2 = nz2 || av[1] != 0.0f;
-    } else if (t >= n4lo && t < n4lo + R4::n) {
-#pragma unroll
-        for (int c = 0; c < C; ++c) lc4[c][t - n4lo] = cv[1][c];
-    } else if (t >= 128 && t < 128 + R3::n) {
-        la3[t - 128] = av[1];
-#pragma unroll
-        for (int c = 0; c < C; ++c) lc3[c][t - 128] = cv[1][c];
-        nz3 = av[1] != 0.0f;
+        for (int c = 0; c < C; ++c) *(L2 && lower ? &lc2[c][256 + t] : &lc3[c][t - 128]) = cv[1][c];
+        if (lower)
+            nz2 = nz2 || av[1] != 0.0f;
+        else
+            nz3 = av[1] != 0.0f;
     }
-    if (nz2) any2 = 1;
-    if (nz3) any3 = 1;
+    if (own4) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) lc4[c][t - n4lo] = cv4[c];
+    }
+    const bool wz2 = __ballot(nz2) != 0, wz3 = __ballot(nz3) != 0;
+    if (l == 0) {
+        sm.any2[w] = wz2;
+        sm.any3[w] = wz3;
+    }
     __syncthreads();
     if (!active) return;
+    const bool any2 = *reinterpret_cast<const unsigned*>(sm.any2) != 0;
+    const bool any3 = *reinterpret_cast<const unsigned*>(sm.any3) != 0;
 
     float out[C][4];
     {
