@@ -235,3 +235,27 @@ def test_lists_with_and_without_the_level_map(W, H, N, level_map):
         same(masks.worklist[i][:k].cpu().numpy().view(np.uint32), pyr.worklist[i], f"list {i}")
     if level_map:
         same(masks.level_map, pyr.level_map, "level map")
+
+
+@pytest.mark.parametrize("R", [1, 2])
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("W,H,N,levels,rel", [(128, 8, 4, 0b1111, 0.05), (128, 40, 2, 0b0011, 0.5),
+                                              (640, 72, 3, 0b0111, 3.0), (1152, 40, 4, 0b1110, 1e-3),
+                                              (256, 64, 3, 0b0101, 1e-14), (256, 64, 3, 0b0111, 1e25)])
+def test_bilateral_windows(W, H, N, levels, rel, f16, R):
+    """Windows cut by every border, across stencil words and ranking tiles
+    (1152 columns: 36 words), and tolerances outside the range of the
+    quotient from one reciprocal."""
+    log(f"[gpu] bilateral {W}x{H} N={N} levels={levels:04b} rel={rel} R={R} f16={f16}")
+    d, n = noisy(W, H, W + H, lo=2.0, hi=6.0)
+    K = scenegen.ssao_kernel(8)
+    mp, omp = mps(N, sigma2=(0.1,) * (N - 1) + (0.0,))
+    nh = n.astype(np.float16) if f16 else n
+    out = mr.mr_frame("ssao", dev(d), dev(nh), F32(80.0), mp, mr.ssao_params(dev(K), 1.0, 0.02),
+                      bilateral=mr.Bilateral(levels=levels, radius=R, depth_rel=rel),
+                      level_dtype=torch.float16 if f16 else torch.float32)
+    torch.cuda.synchronize()
+    ref = oracle.frame("ssao", d, nh.astype(F32), F32(80.0), omp, oracle.SSAOParams(K, 1.0, 0.02),
+                       level_dtype=np.float16 if f16 else None,
+                       bilateral=oracle.BilateralParams(levels=levels, radius=R, depth_rel=rel))
+    same(out, ref.out, "blurred frame")
