@@ -258,8 +258,16 @@ __device__ __forceinline__ void store_out(const EvalLevel& L, unsigned idx, floa
 // P = (X z, Y z, -z), X = ((x + 0.5) - cx) / f, Y = (cy - (y + 0.5)) / f
 __device__ __forceinline__ void view_pos(int x, int y, float z, float f, float cx, float cy,
                                          float& px, float& py, float& pz) {
-    const float X = (((float)x + 0.5f) - cx) / f;
-    const float Y = (cy - ((float)y + 0.5f)) / f;
+    const float nx = ((float)x + 0.5f) - cx, ny = cy - ((float)y + 0.5f);
+    float X, Y;
+    if (QUOT && f >= kFocalLo && f < kFocalHi) {  // uniform: f is the level's
+        const float rcf = recip_fast(f);
+        X = quotient(nx, f, rcf);
+        Y = quotient(ny, f, rcf);
+    } else {
+        X = nx / f;
+        Y = ny / f;
+    }
     px = X * z;
     py = Y * z;
     pz = -z;

@@ -38,17 +38,11 @@ __device__ __forceinline__ BilateralMap bilateral_map(const BilateralArgs& a) {
     return m;
 }
 
-// n / d from rc = 1/d (correctly rounded): two corrections with exact
-// residuals give the division's own rounding for every quotient that can
-// change 1 - n/d, i.e. of at least 2^-26, when d is in [2^-40, 2^60] (no
-// residual is lost below the smallest float; a quotient that overflows
-// leaves a NaN, whose tap takes no part, as the division's does not).
+// The quotient from one reciprocal is the division's for every quotient that
+// can change 1 - n/d, i.e. of at least 2^-26, when d is in this range (no
+// residual is lost below the smallest float; a quotient that overflows leaves
+// a NaN, whose tap takes no part, as the division's does not).
 constexpr float kQuotLo = 0x1p-40f, kQuotHi = 0x1p60f;
-__device__ __forceinline__ float quotient(float n, float d, float rc) {
-    float q = n * rc;
-    q = __builtin_fmaf(__builtin_fmaf(-d, q, n), rc, q);
-    return __builtin_fmaf(__builtin_fmaf(-d, q, n), rc, q);
-}
 
 template <int R, typename VT>
 __device__ __forceinline__ void bilateral_item(const BilateralArgs& a, const BilateralMap& m, unsigned item) {

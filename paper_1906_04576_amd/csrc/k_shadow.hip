@@ -22,7 +22,7 @@ __global__ __launch_bounds__(256) void k_hard(HardArgs a) {
     uint8_t h = 0;
     if (valid_depth(z)) {
         float px, py, pz;
-        view_pos(x, y, z, a.f, 0.5f * (float)a.W, 0.5f * (float)a.H, px, py, pz);
+        view_pos<false>(x, y, z, a.f, 0.5f * (float)a.W, 0.5f * (float)a.H, px, py, pz);
         const LightCoord c = to_light(a.M, a.size, a.fL, px, py, pz);
         if (c.inside) {
             const float thr = c.dr - a.bias;
@@ -75,7 +75,7 @@ template <typename DP>
 __device__ __forceinline__ float pcss_texel(const ShadowArgs& a, const EvalLevel& L, DP bd, DP pd, int x, int y,
                                             float z) {
     float px, py, pz;
-    view_pos(x, y, z, L.f, L.cx, L.cy, px, py, pz);
+    view_pos<false>(x, y, z, L.f, L.cx, L.cy, px, py, pz);
     const LightCoord c = to_light(a.M, a.size, a.fL, px, py, pz);
     if (!c.inside) return 1.0f;
     const ShadowTaps taps{buf_rsrc(a.sm, 4u * (unsigned)a.size * (unsigned)a.size), c.su, c.sv, a.size};

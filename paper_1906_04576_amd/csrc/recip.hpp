@@ -37,4 +37,33 @@ __device__ __forceinline__ float rsqrt_pos(float x) {
     return x < __builtin_inff() ? recip_fast(sqrtf(x)) : 0.0f;
 }
 
+// n / d from rc = 1/d (recip_fast): two corrections with exact residuals
+// (Markstein).  The division's own bits when d, n and n / d are normal and
+// n / d * d * 2^-47 is too, or n = 0: a caller states its ranges.
+__device__ __forceinline__ float quotient(float n, float d, float rc) {
+    float q = n * rc;
+    q = __builtin_fmaf(__builtin_fmaf(-d, q, n), rc, q);
+    return __builtin_fmaf(__builtin_fmaf(-d, q, n), rc, q);
+}
+
+// 1.0f / sqrtf(x) (both rounded) for kRsqrtLo <= x < kRsqrtHi: Goldschmidt's
+// iteration for the square root g with h = 1/(2 g) beside it, the residual
+// x - g g exact in a fused multiply-add, then recip_fast.  The two IEEE
+// operations take 19 instructions, these 11.  tests/native/rsqrt_check.hip
+// compares them for every float of the range.
+constexpr float kRsqrtLo = 0x1p-90f, kRsqrtHi = 0x1p90f;
+__device__ __forceinline__ float rsqrt_fast(float x) {
+    const float y = __builtin_amdgcn_rsqf(x);
+    float g = x * y, h = 0.5f * y;
+    const float e = __builtin_fmaf(-h, g, 0.5f);
+    g = __builtin_fmaf(g, e, g);
+    h = __builtin_fmaf(h, e, h);
+    g = __builtin_fmaf(__builtin_fmaf(-g, g, x), h, g);
+    return recip_fast(g);
+}
+
+// n / f by the division's own bits for |n| = 0 or in [2^-60, 2^60] and a
+// focal length in this range (callers take the division outside it)
+constexpr float kFocalLo = 0x1p-12f, kFocalHi = 0x1p24f;
+
 }  // namespace mr

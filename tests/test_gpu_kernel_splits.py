@@ -14,6 +14,8 @@ bit, so no tolerance is needed):
   * the shadow bits computed inside the edge tiles of a frame;
   * list building with and without the level map in its first launch."""
 import math
+import os
+import subprocess
 import sys
 
 import numpy as np
@@ -125,6 +127,41 @@ def test_sample_groups(effect, S, radius, scale):
         for o, what in zip(outs, ("level depth", "strided depth")):
             same(o[i].cpu().numpy()[..., sel], r[..., sel], f"level {i}, {what}")
     same(plain[1], ref(1, None), "naive pass")
+
+
+def test_fast_reciprocal_square_root_is_exact_over_its_range():
+    """Every float of the range against the IEEE operations (a native program
+    built with the library's flags)."""
+    exe = os.path.join(os.path.dirname(os.path.abspath(__file__)), "native", "_bin", "rsqrt_check")
+    assert os.path.exists(exe), "tests/native programs are not built (run __graft_entry__.build())"
+    log("[gpu] rsqrt_check (exhaustive)")
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=100)
+    log(r.stdout.strip())
+    assert r.returncode == 0 and "mismatches 0" in r.stdout, r.stdout + r.stderr
+
+
+# focal lengths on both sides of the exact quotients' range, radii on both
+# sides of the fast light's, colours and normals of any size
+@pytest.mark.parametrize("focal,radius,scale", [(90.0, 0.5, 1.0), (2.0 ** -13, 0.5, 1.0), (2.0 ** 24, 0.5, 1.0),
+                                                (90.0, 1e-6, 1.0), (90.0, 5e-6, 1.0), (0.01, 2.0, 1.0),
+                                                (90.0, 1.0, 1e-12), (90.0, 1.0, 1e-20), (90.0, 1.0, 1e12)])
+def test_light_ranges(focal, radius, scale):
+    W, H, f = 132, 50, F32(focal)
+    log(f"[gpu] light ranges f={focal} r={radius} normals x {scale}")
+    d, n = noisy(W, H, 77, lo=2.0, hi=2.5)
+    if radius < 1e-3:
+        d = (d * F32(radius)).astype(F32)
+    m = n.copy()
+    rng = np.random.default_rng(3)
+    m[:, rng.random((H, W)) < 0.5] *= F32(scale)
+    m[:, rng.random((H, W)) < 0.1] = 0.0
+    color = (rng.random((3, H, W)) * 1e3).astype(F32)
+    K = scenegen.ssao_kernel(15, seed=5)
+    with np.errstate(all="ignore"):
+        ref = oracle.ssgi_level(d, m, color, f, 1, oracle.SSGIParams(K, radius, 0.02), None)
+    out = mr.mr_eval_ssgi(dev(d), dev(m), dev(color), f, dev(K), radius, 0.02)
+    torch.cuda.synchronize()
+    same(out[1], ref, "naive pass")
 
 
 @pytest.mark.parametrize("nb,npcf,sm", [(1, 1, 1), (2, 7, 5), (7, 8, 64), (8, 9, 256), (9, 16, 3), (17, 33, 128)])
