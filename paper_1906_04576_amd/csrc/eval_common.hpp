@@ -255,7 +255,12 @@ __device__ __forceinline__ void store_out(const EvalLevel& L, unsigned idx, floa
         L.out[idx] = v;
 }
 
-// P = (X z, Y z, -z), X = ((x + 0.5) - cx) / f, Y = (cy - (y + 0.5)) / f
+// P = (X z, Y z, -z), X = ((x + 0.5) - cx) / f, Y = (cy - (y + 0.5)) / f.
+// QUOT: from the reciprocal of f where that is exact, a branch of the wave's:
+// the naive SSAO pass at 4K 236 us (242 us with the divisions).  The shadow
+// pass, with one position per texel ahead of loads that it waits for anyway,
+// divides (frame at 4K 222 us, 223 us with the branch).
+template <bool QUOT = true>
 __device__ __forceinline__ void view_pos(int x, int y, float z, float f, float cx, float cy,
                                          float& px, float& py, float& pz) {
     const float nx = ((float)x + 0.5f) - cx, ny = cy - ((float)y + 0.5f);
