@@ -83,42 +83,72 @@ hipError_t launch_ssao_batch(const SsaoArgs* T, int n, int S, int normal_dtype, 
 // those evaluations are skipped without changing a bit (all values are
 // finite).  The loop over levels is uniform; lanes take part where their
 // pixel needs the level.
+//
+// A block's work is short (256 pixels), so what it waits for beside the
+// samples counts: a level's samples are staged by a wave of its own, the
+// taps' values come for all levels before any stencil byte, and the stencil
+// is read where a value is not 0.  Masks and this pass at 1080p, samples 32,
+// 16, 8, 4: 143.5 us with eight loads and two divisions per level and the
+// levels staged one after another, 136 us without those, 129.5 us staged by
+// one wave each.  6 waves per SIMD (5 unasked: 142 us instead of 136; at 8
+// the spilled registers cost 10 us).
 
-// alpha_i at full-res pixel (x, y): min(A w, 1), A the bilinear of a_i
-// (texel centres, clamp to edge), 0 where none of the four taps is in the
-// stencil; sums from +0 in tap order
-__device__ __forceinline__ float fullres_alpha(const FullresLevel& V, int x, int y) {
-    const float s = (float)(1 << V.sh);
-    const float u = ((float)x + 0.5f) / s - 0.5f, v = ((float)y + 0.5f) / s - 0.5f;
+// The taps of level i around full-res pixel (x, y): texel centres, clamped
+// to the edge.  (u = (x + 0.5) / s - 0.5; the scaling by a power of two is
+// exact.)
+struct FullresTaps {
+    float b[4];
+    unsigned p[4];
+};
+
+__device__ __forceinline__ FullresTaps fullres_taps(const FullresLevel& V, int x, int y) {
+    const float is = __uint_as_float((127u - (unsigned)V.sh) << 23);  // 1 / s
+    const float u = ((float)x + 0.5f) * is - 0.5f, v = ((float)y + 0.5f) * is - 0.5f;
     const float ux = floorf(u), vy = floorf(v);
     const float fx = u - ux, fy = v - vy;
     const int x0 = (int)ux, y0 = (int)vy;
     const int xa = min(max(x0, 0), V.W - 1), xb = min(max(x0 + 1, 0), V.W - 1);
     const int ya = min(max(y0, 0), V.H - 1), yb = min(max(y0 + 1, 0), V.H - 1);
-    const float b0 = (1.0f - fx) * (1.0f - fy), b1 = fx * (1.0f - fy), b2 = (1.0f - fx) * fy, b3 = fx * fy;
     const unsigned r0 = (unsigned)ya * (unsigned)V.W, r1 = (unsigned)yb * (unsigned)V.W;
-    float den = 0.0f;
-    den = den + (V.S[r0 + xa] ? b0 : 0.0f);
-    den = den + (V.S[r0 + xb] ? b1 : 0.0f);
-    den = den + (V.S[r1 + xa] ? b2 : 0.0f);
-    den = den + (V.S[r1 + xb] ? b3 : 0.0f);
+    return {{(1.0f - fx) * (1.0f - fy), fx * (1.0f - fy), (1.0f - fx) * fy, fx * fy},
+            {r0 + xa, r0 + xb, r1 + xa, r1 + xb}};
+}
+
+// A, the bilinear of a_i; sums from +0 in tap order.  At scale 1 the pixel's
+// own texel has weight 1 and the others add +0.
+__device__ __forceinline__ float fullres_a(const FullresLevel& V, int x, int y) {
+    if (V.sh == 0) return V.a[(unsigned)y * (unsigned)V.W + (unsigned)x];
+    const FullresTaps t = fullres_taps(V, x, y);
     float A = 0.0f;
-    A = A + b0 * V.a[r0 + xa];
-    A = A + b1 * V.a[r0 + xb];
-    A = A + b2 * V.a[r1 + xa];
-    A = A + b3 * V.a[r1 + xb];
-    return den > 0.0f ? fminf(A * V.w, 1.0f) : 0.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) A = A + t.b[k] * V.a[t.p[k]];
+    return A;
+}
+
+// alpha_i = min(A w, 1), 0 where none of the four taps is in the stencil.
+// The stencil is read where A is not 0 only: otherwise alpha_i is 0 either way.
+__device__ __forceinline__ float fullres_alpha(const FullresLevel& V, float A, int x, int y) {
+    if (A == 0.0f) return 0.0f;
+    bool in;
+    if (V.sh == 0) {
+        in = V.S[(unsigned)y * (unsigned)V.W + (unsigned)x] != 0;
+    } else {
+        const FullresTaps t = fullres_taps(V, x, y);
+        in = false;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) in = in | ((V.S[t.p[k]] != 0) & (t.b[k] > 0.0f));
+    }
+    return in ? fminf(A * V.w, 1.0f) : 0.0f;
 }
 
 template <typename NT>
-__global__ __launch_bounds__(256) void k_ssao_fullres(FullresArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_ssao_fullres(FullresArgs a) {
     __shared__ float ks[3 * kFullresMaxSamples];
     __shared__ unsigned kmax_bits[kMaxLevels];  // per level, as bits: all values >= 0
     // per-level sampling parameters in LDS: indexing the kernel argument by the
     // level loop would copy it to scratch
     __shared__ SsaoSampling sp[kMaxLevels];
     __shared__ int skoff[kMaxLevels];
-    if (threadIdx.x < kMaxLevels) kmax_bits[threadIdx.x] = 0u;
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int j = 0; j < kMaxLevels; ++j) {
@@ -126,17 +156,17 @@ __global__ __launch_bounds__(256) void k_ssao_fullres(FullresArgs a) {
             skoff[j] = a.lv[j].koff;
         }
     }
-    __syncthreads();
-    for (int j = 0; j < a.nlev; ++j) {
+    // a wave per level: their loads are in flight together
+    for (int j = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); j < a.nlev; j += 4) {
         const FullresLevel& V = a.lv[j];
         unsigned m = 0u;
-        for (int i = threadIdx.x; i < 3 * V.p.S; i += 256) {
+        for (int i = (int)__lane_id(); i < 3 * V.p.S; i += 64) {
             const float v = V.p.kernel[i];
             ks[3 * V.koff + i] = v;
             m = max(m, __float_as_uint(fabsf(v)));
         }
         for (int o = 32; o >= 1; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o, 64));
-        if (__lane_id() == 0) atomicMax(&kmax_bits[j], m);
+        if (__lane_id() == 0) kmax_bits[j] = m;
     }
     __syncthreads();
     const EvalLevel& L = a.L;
@@ -155,12 +185,11 @@ __global__ __launch_bounds__(256) void k_ssao_fullres(FullresArgs a) {
         float al[kMaxLevels - 1];
         int k = top;  // finest level with alpha 1, else the coarsest
 #pragma unroll
+        for (int j = kMaxLevels - 2; j >= 0; --j) al[j] = j < top ? fullres_a(a.lv[j], x, y) : 0.0f;
+#pragma unroll
         for (int j = kMaxLevels - 2; j >= 0; --j) {
-            al[j] = 0.0f;
-            if (j < top && geo) {
-                al[j] = fullres_alpha(a.lv[j], x, y);
-                if (al[j] == 1.0f) k = j;
-            }
+            al[j] = j < top && geo ? fullres_alpha(a.lv[j], al[j], x, y) : 0.0f;
+            if (al[j] == 1.0f) k = j;
         }
         float c = 0.0f;
         for (int j = top; j >= 0; --j) {
