@@ -152,26 +152,32 @@ __device__ __forceinline__ unsigned test_samples(const SampleTexel& T, const Sam
 }
 
 // Per block: the S samples (at most kLdsSamples) in LDS, and the largest
-// |component| of them (+inf when not staged); ends with a barrier.
-template <bool KLDS>
-__device__ __forceinline__ float stage_samples(const float* kernel, int S, float* ks) {
-    __shared__ unsigned kmax_bits;  // as bits: all values >= 0
+// |component| of them (+inf when not staged); ends with its one barrier.
+// meanwhile() runs while the samples are on their way.  (With a barrier
+// before the loads and the row sums ahead of them the naive pass at 4K, a
+// block of which stages for 256 texels, took 238 us, now 233 us.)
+template <bool KLDS, typename F>
+__device__ __forceinline__ float stage_samples(const float* kernel, int S, float* ks, F meanwhile) {
     if (!KLDS) {
+        meanwhile();
         __syncthreads();
         return __builtin_inff();
     }
-    if (threadIdx.x == 0) kmax_bits = 0u;
-    __syncthreads();
-    unsigned m = 0u;
-    for (int i = threadIdx.x; i < 3 * S; i += 256) {
-        const float v = kernel[i];
-        ks[i] = v;
-        m = max(m, __float_as_uint(fabsf(v)));
+    __shared__ unsigned wmax[4];  // per wave, as bits: all values >= 0
+    const int t = (int)threadIdx.x, n = 3 * S;
+    const float v = t < n ? kernel[t] : 0.0f;
+    meanwhile();
+    unsigned m = __float_as_uint(fabsf(v));
+    if (t < n) ks[t] = v;
+    for (int i = t + 256; i < n; i += 256) {
+        const float u = kernel[i];
+        ks[i] = u;
+        m = max(m, __float_as_uint(fabsf(u)));
     }
     for (int o = 32; o >= 1; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o, 64));
-    if (__lane_id() == 0) atomicMax(&kmax_bits, m);
+    if (__lane_id() == 0) wmax[t >> 6] = m;
     __syncthreads();
-    return __uint_as_float(kmax_bits);
+    return __uint_as_float(max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3])));
 }
 
 }  // namespace mr

@@ -253,8 +253,9 @@ constexpr int kTiledSamples = 256;
 // the largest |component| of the samples (+inf when not staged).
 template <bool AL, bool KLDS>
 __device__ __forceinline__ float ssao_stage(const SsaoArgs& a, float* ks, float* rows) {
-    if (AL) stage_rows(a.c, rows);
-    return stage_samples<KLDS>(a.kernel, a.S, ks);
+    return stage_samples<KLDS>(a.kernel, a.S, ks, [&] {
+        if (AL) stage_rows(a.c, rows);
+    });
 }
 
 }  // namespace mr

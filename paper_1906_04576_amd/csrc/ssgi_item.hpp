@@ -211,8 +211,9 @@ __device__ __forceinline__ void ssgi_items(const SsgiArgs& a, KP K, float kmax, 
 // the largest |component| of the samples (+inf when not staged).
 template <bool AL, bool KLDS>
 __device__ __forceinline__ float ssgi_stage(const SsgiArgs& a, float* ks, float* rows) {
-    if (AL) stage_rows(a.c, rows);
-    return stage_samples<KLDS>(a.kernel, a.S, ks);
+    return stage_samples<KLDS>(a.kernel, a.S, ks, [&] {
+        if (AL) stage_rows(a.c, rows);
+    });
 }
 
 }  // namespace mr
