@@ -19,8 +19,9 @@ constexpr unsigned kFusedListStage = 4096;
 
 // ranking tiles per ticket of the stencil and list passes: every finished
 // ticket writes its XCD's L2 back, so fewer, larger tickets cost fewer
-// write-backs (24-frame SSGI batch: 3.61 ms with one tile per ticket, 3.48
-// with 4, 3.42 with 8, 3.40 with 16)
+// write-backs (24-frame SSGI batch: 2.69 ms with one tile per ticket, 2.54
+// with 4, 2.47 with 8, 2.46 with 16; four frames at 1280 x 720, with fewer
+// tickets than blocks: 0.575, 0.525, 0.540 and 0.583 ms)
 constexpr unsigned kFusedRankGroup = 8;
 
 // counter words (see FusedArgs)
@@ -85,24 +86,21 @@ __device__ __forceinline__ unsigned fused_bcast(unsigned* slot, unsigned v) {
     return r;
 }
 
-// Stage calls through restrict-qualified table parameters: inlined, they
-// keep the tables' no-alias guarantee, so a frame's fields need not be read
-// again after the stage's own stores.
-template <typename NT>
-__device__ __forceinline__ void fused_edges(const EdgeArgs* __restrict__ te, int f, unsigned i, unsigned tx) {
-    edges_tile<NT, false, true, true>(te[f], i, tx);
+// Entry f (wave-uniform) of a table that nothing writes while the launch runs,
+// read through the constant address space: its fields then come by scalar
+// loads into scalar registers, whatever the kernel has stored or waited for
+// in between.  (Read as ordinary memory, every field came into a vector
+// register by a flat load, again after each fence, atomic and store: 24 uneven
+// SSGI frames 3.89 ms, now 2.47 ms; 24 SSAO frames 2.34 ms, now 1.70 ms.)
+template <typename T>
+__device__ __forceinline__ const T& fused_table(const void* t, unsigned f) {
+    typedef const T __attribute__((address_space(4))) CT;
+    return *(const T*)((CT*)(unsigned long long)t + f);
 }
-template <bool LIST, typename LDS>
-__device__ __forceinline__ void fused_rank(const LeanArgs* __restrict__ tl, int f, unsigned i, LDS& sm) {
-    if constexpr (LIST)
-        list_block<256, kFusedListStage>(tl[f], i, sm);
-    else
-        stencil_block<256>(tl[f], i, sm);
-}
-template <int C, typename VT, typename LDS>
-__device__ __forceinline__ void fused_merge4(const LeanMergeArgs* __restrict__ tm, int f, unsigned i, unsigned tx,
-                                             LDS& sm) {
-    merge4_tile<C, VT>(tm[f], i, tx, sm);
+
+// a frame's tiles in a stage
+__device__ __forceinline__ unsigned fused_tiles(const FusedArgs& A, int stage, int f) {
+    return fused_table<unsigned>(A.base[stage], f + 1) - fused_table<unsigned>(A.base[stage], f);
 }
 
 template <int C>
@@ -133,9 +131,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     __shared__ unsigned tb[kFusedStages][kMaxBatchFrames + 1];
     float kmax = 0.0f;
     if constexpr (EFFECT == MR_EFFECT_SSAO) {
-        kmax = ssao_stage<true, true>(static_cast<const SsaoArgs*>(A.tv)[0], ks, rows);
+        kmax = ssao_stage<true, true>(fused_table<SsaoArgs>(A.tv, 0), ks, rows);
     } else {
-        kmax = ssgi_stage<true, true>(static_cast<const SsgiArgs*>(A.tv)[0], ks, rows);
+        kmax = ssgi_stage<true, true>(fused_table<SsgiArgs>(A.tv, 0), ks, rows);
     }
     const unsigned G = (unsigned)A.group;
     if (threadIdx.x < 64) {
@@ -190,26 +188,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         // tiles [j G, min((j + 1) G, n)) of the frame's edge or merge tiles
         const unsigned tile0 = j * G;
         if (s == 0) {
-            const unsigned nt = A.base[0][f + 1] - A.base[0][f];
+            const unsigned nt = fused_tiles(A, 0, f);
             for (unsigned i = tile0; i < nt && i < tile0 + G; ++i) {
                 if (i > tile0) __syncthreads();  // the previous tile's LDS reads are done
-                fused_edges<NT>(A.te, f, i, A.edge_tx[f]);
+                edges_tile<NT, false, true, true>(fused_table<EdgeArgs>(A.te, f), i, fused_table<unsigned>(A.edge_tx, f));
             }
         } else if (s == 1 || s == 2) {
             // ranking tiles [j R, min((j + 1) R, n)): the stencil pass, or the
             // list pass (which waited for the frame's whole stencil pass)
-            const unsigned nt = A.base[1][f + 1] - A.base[1][f];
+            const unsigned nt = fused_tiles(A, 1, f);
             for (unsigned i = j * kFusedRankGroup; i < nt && i < (j + 1u) * kFusedRankGroup; ++i) {
                 if (i > j * kFusedRankGroup) __syncthreads();  // the previous tile's LDS reads are done
                 if (s == 1)
-                    fused_rank<false>(A.tl, f, i, u.st);
+                    stencil_block<256>(fused_table<LeanArgs>(A.tl, f), i, u.st);
                 else
-                    fused_rank<true>(A.tl, f, i, u.li);
+                    list_block<256, kFusedListStage>(fused_table<LeanArgs>(A.tl, f), i, u.li);
             }
         } else if (s == 3) {
             // an evaluation worker: chunks of the frame's items until none is left
             using Args = std::conditional_t<EFFECT == MR_EFFECT_SSAO, SsaoArgs, SsgiArgs>;
-            const Args& a = static_cast<const Args*>(A.tv)[f];
+            const Args& a = fused_table<Args>(A.tv, f);
             const ItemMap m = make_item_map(a.c);
             const unsigned items = item_total(m), per = 256u * (unsigned)A.items;
             const unsigned nch = (items + per - 1u) / per;
@@ -233,20 +231,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                 }
             }
         } else {
-            const LeanMergeArgs& ma = A.tm[f];
-            const unsigned nt = A.base[4][f + 1] - A.base[4][f];
+            const LeanMergeArgs& ma = fused_table<LeanMergeArgs>(A.tm, f);
+            const unsigned tx = fused_table<unsigned>(A.merge_tx, f);
+            const unsigned nt = fused_tiles(A, 4, f);
             for (unsigned i = tile0; i < nt && i < tile0 + G; ++i) {
                 if (i > tile0) __syncthreads();  // the previous tile's LDS reads are done
                 if constexpr (M4) {
                     if (ma.c16)
-                        fused_merge4<C, _Float16>(A.tm, f, i, A.merge_tx[f], u.m4);
+                        merge4_tile<C, _Float16>(ma, i, tx, u.m4);
                     else
-                        fused_merge4<C, float>(A.tm, f, i, A.merge_tx[f], u.m4);
+                        merge4_tile<C, float>(ma, i, tx, u.m4);
                 } else {
                     if (ma.c16)
-                        merge_tile<C, _Float16>(ma, i, A.merge_tx[f], u.mg.la, u.mg.ls, u.mg.lc, u.mg.lvl_any);
+                        merge_tile<C, _Float16>(ma, i, tx, u.mg.la, u.mg.ls, u.mg.lc, u.mg.lvl_any);
                     else
-                        merge_tile<C, float>(ma, i, A.merge_tx[f], u.mg.la, u.mg.ls, u.mg.lc, u.mg.lvl_any);
+                        merge_tile<C, float>(ma, i, tx, u.mg.la, u.mg.ls, u.mg.lc, u.mg.lvl_any);
                 }
             }
         }

@@ -53,10 +53,11 @@ __device__ __forceinline__ float ld(const T* p, long long i) {
 // values are never used.
 //
 // Every lane of a wave passes the same p and bytes, but the compiler may hold
-// them in vector registers (frame tables that a kernel reads after its own
-// stores); without the scalar copy each load through such a buffer becomes a
-// loop over the lanes' values (persistent SSGI batch: 4.6 ms, 3.8 ms without
-// those loops in the evaluation; the other launches are unchanged).
+// them in vector registers (scalars that the persistent batch kernel spilled
+// to lanes, fields read after a kernel's own stores); without the scalar copy
+// each load through such a buffer becomes a loop over the lanes' values (the
+// persistent SSGI batch was 4.6 ms with those loops in its evaluation, 3.8 ms
+// without; the other launches are unchanged).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, unsigned bytes) {
     const unsigned long long v = (unsigned long long)p;
     const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
