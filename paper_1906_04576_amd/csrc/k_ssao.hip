@@ -17,14 +17,13 @@ __global__ __launch_bounds__(256) void k_ssao(SsaoArgs a) {
 
 // The compact frame path with the coarsest level in 16 x 16 tiles whose depth
 // (with a halo of H texels) is staged in LDS; at most kTiledSamples samples,
-// staged in LDS as well.
+// staged in LDS as well.  8 waves per SIMD, in registers and in LDS.
 template <typename NT, int H>
-__global__ __launch_bounds__(256) void k_ssao_tiled(SsaoArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_ssao_tiled(SsaoArgs a) {
     __shared__ float ks[3 * kTiledSamples];
-    __shared__ float rows[kRowLevels * kRowTable];
-    __shared__ float zt[(kDenseTile + 2 * H) * (kDenseTile + 2 * H)];
-    const float kmax = ssao_stage<true, true>(a, ks, rows);
-    ssao_items_tiled<NT, H>(a, ks, rows, kmax, zt);
+    __shared__ float zt[(kDenseTile + 2 * H) * (kDenseTile + 2 * H)];  // the row tables first
+    const float kmax = ssao_stage<true, true>(a, ks, zt);
+    ssao_items_tiled<NT, H>(a, ks, zt, kmax);
 }
 
 // Frames of a batch (same samples, mask and effect parameters): one item
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
             const bool need = geo && (j == k || (j < k && alj > 0.0f));
             if (__ballot(need) == 0) continue;
             if (need) {
-                const float v = ssao_texel(sp[j], L, n, (const float*)ks + 3 * skoff[j],
+                const float v = ssao_texel<kGroup>(sp[j], L, n, (const float*)ks + 3 * skoff[j],
                                            __uint_as_float(kmax_bits[j]), x, y, z);
                 c = j == k ? v : v * alj + c * (1.0f - alj);
             }

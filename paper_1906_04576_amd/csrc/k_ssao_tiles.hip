@@ -9,9 +9,13 @@ namespace mr {
 // whose depth, with a halo of H texels, is staged in LDS (as k_ssao_tiled):
 // one item space over all frames, each frame's range padded to whole chunks
 // of 256, swept by a resident grid in fixed strides.  At most kTiledSamples
-// samples.
+// samples.  8 waves per SIMD (7 in LDS at H = 24, where a frame's list chunks
+// follow another's tiles, so that the row tables need LDS of their own): 24
+// uneven frames, halos 8, 16, 24, 904, 911, 916 us with 5 waves, now 872, 873
+// and 876 us.
 template <typename NT, int H>
-__global__ __launch_bounds__(256) void k_ssao_batch_tiled(const SsaoArgs* __restrict__ T, int n) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(H == 24 ? 7 : 8)))
+void k_ssao_batch_tiled(const SsaoArgs* __restrict__ T, int n) {
     __shared__ float ks[3 * kTiledSamples];
     __shared__ float rows[kRowLevels * kRowTable];
     __shared__ float zt[(kDenseTile + 2 * H) * (kDenseTile + 2 * H)];

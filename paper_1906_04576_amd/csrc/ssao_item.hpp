@@ -17,6 +17,13 @@ struct DepthTile {
     unsigned x0, y0, tw;
 };
 
+// samples in flight together in the launches with depth tiles: their waves do
+// not wait for as many gathers, and groups of 8 (84 to 89 registers, 5 waves
+// per SIMD) left them behind the plane form.  Frame at 3840 x 2160 with 64
+// samples, halos 8, 16, 24: 123.1, 124.8, 125.7 us with groups of 8; 116.2,
+// 118.0, 118.1 us with groups of 4 and 8 waves per SIMD; groups of 2 within 1 %.
+constexpr int kTileGroup = 4;
+
 // gathers from a staged square of on-screen texels, else from the plane
 struct TileGather {
     __amdgpu_buffer_rsrc_t rz;
@@ -29,11 +36,11 @@ struct TileGather {
     }
 };
 
-// Occluding samples of one texel.  FAST: in groups of kGroup samples, the
-// gathers of one group in flight while the one before is tested (measured on
+// Occluding samples of one texel.  FAST: in groups of N samples, the gathers
+// of one group in flight while the one before is tested (kGroup measured on
 // multi-resolution frames: 3840 x 2160 104.7 us for groups of 4 and 101.6 us
 // for groups of 8, with fewer waves but twice the gathers in flight).
-template <bool FAST, typename SA, typename KP, typename GF>
+template <bool FAST, int N, typename SA, typename KP, typename GF>
 __device__ __forceinline__ int ssao_count(const SA& a, const EvalLevel& L, KP K, const SampleTexel& T,
                                           const GF& gather) {
     const float r = a.r, b = a.b;
@@ -41,29 +48,29 @@ __device__ __forceinline__ int ssao_count(const SA& a, const EvalLevel& L, KP K,
     int occ = 0, s = 0;
     if constexpr (FAST) {
         auto count = [&](const auto& g) { return __popc(test_samples(T, g, r, b, 0u)); };
-        if (S >= kGroup) {
-            SampleGroup<kGroup> A, B;
+        if (S >= N) {
+            SampleGroup<N> A, B;
             issue_samples(L, K, 0, T, gather, A);
-            for (s = kGroup; s + 2 * kGroup <= S; s += 2 * kGroup) {
+            for (s = N; s + 2 * N <= S; s += 2 * N) {
                 issue_samples(L, K, s, T, gather, B);
                 occ += count(A);
-                issue_samples(L, K, s + kGroup, T, gather, A);
+                issue_samples(L, K, s + N, T, gather, A);
                 occ += count(B);
             }
-            if (s + kGroup <= S) {
+            if (s + N <= S) {
                 issue_samples(L, K, s, T, gather, B);
                 occ += count(A);
                 occ += count(B);
-                s += kGroup;
+                s += N;
             } else {
                 occ += count(A);
             }
         }
-        if (s + kGroup / 2 <= S) {
-            SampleGroup<kGroup / 2> A;
+        if (N >= 8 && s + N / 2 <= S) {
+            SampleGroup<N / 2> A;
             issue_samples(L, K, s, T, gather, A);
             occ += count(A);
-            s += kGroup / 2;
+            s += N / 2;
         }
         for (; s < S; ++s) {
             SampleGroup<1> A;
@@ -100,14 +107,15 @@ __device__ __forceinline__ int ssao_count(const SA& a, const EvalLevel& L, KP K,
 // occlusion of one texel; K points to LDS (staged samples) or global memory;
 // kmax as in fast_samples; a holds the sampling parameters r, b and S
 // (SsaoArgs or SsaoSampling); dt: TILE, the staged square
-template <bool TILE = false, typename SA, typename KP>
+template <int N, bool TILE = false, typename SA, typename KP>
 __device__ __forceinline__ float ssao_texel(const SA& a, const EvalLevel& L, const Normal& n, KP K, float kmax, int x,
                                             int y, float z, const DepthTile& dt = DepthTile{}) {
     const SampleTexel T = sample_texel(L, n, a.r, x, y, z);
     const unsigned last = last_texel(L);
     const __amdgpu_buffer_rsrc_t rz = buf_rsrc(L.z, last + 4u);
     auto count = [&](const auto& gather) {
-        return fast_samples(T, kmax, a.r) ? ssao_count<true>(a, L, K, T, gather) : ssao_count<false>(a, L, K, T, gather);
+        return fast_samples(T, kmax, a.r) ? ssao_count<true, N>(a, L, K, T, gather)
+                                        : ssao_count<false, N>(a, L, K, T, gather);
     };
     int occ;
     if constexpr (TILE)
@@ -118,7 +126,7 @@ __device__ __forceinline__ float ssao_texel(const SA& a, const EvalLevel& L, con
 }
 
 // one item (a listed texel, or a texel of a dense level)
-template <typename NT, bool KLDS, bool AL>
+template <typename NT, bool KLDS, bool AL, int N = kGroup>
 __device__ __forceinline__ void ssao_item(const SsaoArgs& a, const ItemMap& m, unsigned item, const float* ks,
                                           const float* rows, float kmax) {
     const NT* nrm = static_cast<const NT*>(a.c.normal);
@@ -137,9 +145,9 @@ __device__ __forceinline__ void ssao_item(const SsaoArgs& a, const ItemMap& m, u
     float res = 0.0f;
     if (valid_depth(z)) {
         if (KLDS)
-            res = ssao_texel(a, L, n, ks, kmax, x, y, z);
+            res = ssao_texel<N>(a, L, n, ks, kmax, x, y, z);
         else
-            res = ssao_texel(a, L, n, a.kernel, kmax, x, y, z);
+            res = ssao_texel<N>(a, L, n, a.kernel, kmax, x, y, z);
     }
     store_out(L, L.compact ? local : (unsigned)y * (unsigned)L.W + (unsigned)x, res);
 }
@@ -160,11 +168,12 @@ __device__ __forceinline__ void ssao_items(const SsaoArgs& a, const float* ks, c
 // (16 + 2H)^2 floats) before its texels' samples gather: the samples that
 // land in the staged square read it there.  Values outside the level are
 // staged clamped; only off-screen samples, which never count, can reach
-// them.  The list levels' chunks run as in ssao_items.
+// them.  The list levels' chunks run as in ssao_items; they come first in a
+// block's sweep, so that zt takes over the LDS of their row tables.
 template <typename NT, int H>
-__device__ __forceinline__ void ssao_items_tiled(const SsaoArgs& a, const float* ks, const float* rows, float kmax,
-                                                 float* zt) {
+__device__ __forceinline__ void ssao_items_tiled(const SsaoArgs& a, const float* ks, float* zt, float kmax) {
     constexpr int TW = kDenseTile + 2 * H;
+    static_assert(TW * TW >= kRowLevels * kRowTable, "the row tables lie in the depth tile's LDS");
     const ItemMap m = make_item_map(a.c);
     const unsigned total = item_total(m);
     const int jd = m.nlev - 1;  // the dense coarsest level
@@ -177,12 +186,13 @@ __device__ __forceinline__ void ssao_items_tiled(const SsaoArgs& a, const float*
     for (unsigned c = cr.first; c < cr.end; c += cr.step) {
         if (c * 256u < dense0) {
             const unsigned item = c * 256u + threadIdx.x;
-            if (item < total) ssao_item<NT, true, true>(a, m, item, ks, rows, kmax);
+            if (item < total) ssao_item<NT, true, true, kTileGroup>(a, m, item, ks, zt, kmax);
             continue;
         }
         const EvalLevel& L = a.c.lv[jd];
         const unsigned tile = c - dense0 / 256u, tx = dense_tiles_x(L.W);
         const int x0 = (int)(tile % tx) * kDenseTile, y0 = (int)(tile / tx) * kDenseTile;
+        __syncthreads();  // all reads of the row tables or of the tile before are done
         for (int i = threadIdx.x; i < TW * TW; i += 256) {
             const int ry = i / TW, rx = i - ry * TW;
             const int gx = min(max(x0 - H + rx, 0), L.W - 1), gy = min(max(y0 - H + ry, 0), L.H - 1);
@@ -195,11 +205,10 @@ __device__ __forceinline__ void ssao_items_tiled(const SsaoArgs& a, const float*
             float res = 0.0f;
             if (valid_depth(z)) {
                 const DepthTile dt{zt, (unsigned)(x0 - H), (unsigned)(y0 - H), (unsigned)TW};
-                res = ssao_texel<true>(a, L, texel_normal(L, nrm, plane, x, y), ks, kmax, x, y, z, dt);
+                res = ssao_texel<kTileGroup, true>(a, L, texel_normal(L, nrm, plane, x, y), ks, kmax, x, y, z, dt);
             }
             store_out(L, (unsigned)y * (unsigned)L.W + (unsigned)x, res);
         }
-        __syncthreads();  // the next tile's staging overwrites zt
     }
 }
 
@@ -219,7 +228,7 @@ __device__ __forceinline__ void ssao_chunk_tiled(const SsaoArgs& a, const ItemMa
     for (int k = 0; k < kMaxLevels; ++k) dense0 = k == jd ? m.cum[k] : dense0;
     if (c * 256u < dense0) {
         const unsigned item = c * 256u + threadIdx.x;
-        if (item < total) ssao_item<NT, true, true>(a, m, item, ks, rows, kmax);
+        if (item < total) ssao_item<NT, true, true, kTileGroup>(a, m, item, ks, rows, kmax);
         return;
     }
     const NT* nrm = static_cast<const NT*>(a.c.normal);
@@ -239,7 +248,7 @@ __device__ __forceinline__ void ssao_chunk_tiled(const SsaoArgs& a, const ItemMa
         float res = 0.0f;
         if (valid_depth(z)) {
             const DepthTile dt{zt, (unsigned)(x0 - H), (unsigned)(y0 - H), (unsigned)TW};
-            res = ssao_texel<true>(a, L, texel_normal(L, nrm, plane, x, y), ks, kmax, x, y, z, dt);
+            res = ssao_texel<kTileGroup, true>(a, L, texel_normal(L, nrm, plane, x, y), ks, kmax, x, y, z, dt);
         }
         store_out(L, (unsigned)y * (unsigned)L.W + (unsigned)x, res);
     }
