@@ -31,7 +31,7 @@ __device__ __forceinline__ SampleTexel sample_texel(const EvalLevel& L, const No
 }
 
 // Whether the fast forms below hold for every sample of the wave's texels;
-// kmax = the largest |component| over the samples (+inf when unknown).
+// kmax = the largest |component| over the samples.
 // Every sample's d = z - (kx rtz + ky rbz + kz rnz) (rounded) lies within
 // Bz = kmax (|rtz| + |rbz| + |rnz|) of z, up to a relative 2^-21; with these
 // margins all d are in [2^-126, 2^126), where recip_fast is exact.  Sample
@@ -74,9 +74,11 @@ __device__ __forceinline__ void project_fast(const EvalLevel& L, KP K, int s, co
           (out & 0x80000000u);
 }
 
-// Any sample: the division, and the bounds by compares.  off: the offset of
-// the sample's texel, of texel (0, 0) when it is off screen.
-template <typename KP>
+// Any sample: the bounds by compares, 1/d by recip_pos (RCP) or the division.
+// off: the offset of the sample's texel, of texel (0, 0) when it is off screen.
+// (RCP pays in SSGI's launches; in SSAO's it takes registers that the fast form
+// needs more: batch of three with radius 8 122 us, 120 us with the division.)
+template <bool RCP, typename KP>
 __device__ __forceinline__ void project_any(const EvalLevel& L, KP K, int s, const SampleTexel& T, bool& on, float& d,
                                             unsigned& off, int& x, int& y) {
     const float Wf = (float)L.W, Hf = (float)L.H;
@@ -85,7 +87,7 @@ __device__ __forceinline__ void project_any(const EvalLevel& L, KP K, int s, con
     d = -qz;
     const float qx = ((T.px + kx * T.rtx) + ky * T.rbx) + kz * T.rnx;
     const float qy = ((T.py + kx * T.rty) + ky * T.rby) + kz * T.rny;
-    const float inv = 1.0f / d;
+    const float inv = RCP ? recip_pos(d) : 1.0f / d;  // the same where d > 0, else unused
     const float u = L.cx + (qx * inv) * L.f;
     const float v = L.cy - (qy * inv) * L.f;
     on = (d > 0.0f) & (u >= 0.0f) & (u < Wf) & (v >= 0.0f) & (v < Hf);
@@ -151,27 +153,24 @@ __device__ __forceinline__ unsigned test_samples(const SampleTexel& T, const Sam
     return hits;
 }
 
-// Per block: the S samples (at most kLdsSamples) in LDS, and the largest
-// |component| of them (+inf when not staged); ends with its one barrier.
+// Per block: the S samples in LDS (KLDS: at most kLdsSamples), and the largest
+// |component| of them; ends with its one barrier.  (Without the maximum of a
+// set that is not staged, all its waves took the general form: 1025 samples,
+// SSGI frame at 1280 x 720 786 us, now 610 us; naive SSAO pass 1031 and 924 us.)
 // meanwhile() runs while the samples are on their way.  (With a barrier
 // before the loads and the row sums ahead of them the naive pass at 4K, a
 // block of which stages for 256 texels, took 238 us, now 233 us.)
 template <bool KLDS, typename F>
 __device__ __forceinline__ float stage_samples(const float* kernel, int S, float* ks, F meanwhile) {
-    if (!KLDS) {
-        meanwhile();
-        __syncthreads();
-        return __builtin_inff();
-    }
     __shared__ unsigned wmax[4];  // per wave, as bits: all values >= 0
     const int t = (int)threadIdx.x, n = 3 * S;
     const float v = t < n ? kernel[t] : 0.0f;
     meanwhile();
     unsigned m = __float_as_uint(fabsf(v));
-    if (t < n) ks[t] = v;
+    if (KLDS && t < n) ks[t] = v;
     for (int i = t + 256; i < n; i += 256) {
         const float u = kernel[i];
-        ks[i] = u;
+        if (KLDS) ks[i] = u;
         m = max(m, __float_as_uint(fabsf(u)));
     }
     for (int o = 32; o >= 1; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o, 64));

@@ -86,7 +86,7 @@ __device__ __forceinline__ int ssao_count(const SA& a, const EvalLevel& L, KP K,
             for (int k = 0; k < G; ++k) {
                 unsigned off;
                 int x, y;
-                project_any(L, K, s + k, T, on[k], d[k], off, x, y);
+                project_any<false>(L, K, s + k, T, on[k], d[k], off, x, y);
                 zs[k] = gather(off, x, y);
             }
 #pragma unroll
@@ -97,7 +97,7 @@ __device__ __forceinline__ int ssao_count(const SA& a, const EvalLevel& L, KP K,
             float d;
             unsigned off;
             int x, y;
-            project_any(L, K, s, T, on, d, off, x, y);
+            project_any<false>(L, K, s, T, on, d, off, x, y);
             occ += occludes_any(on, T.z, d, gather(off, x, y), r, b) ? 1 : 0;
         }
     }
@@ -259,7 +259,7 @@ __device__ __forceinline__ void ssao_chunk_tiled(const SsaoArgs& a, const ItemMa
 constexpr int kTiledSamples = 256;
 
 // Per block: the blur's row sums (AL) and, KLDS, the samples in LDS; returns
-// the largest |component| of the samples (+inf when not staged).
+// the largest |component| of the samples.
 template <bool AL, bool KLDS>
 __device__ __forceinline__ float ssao_stage(const SsaoArgs& a, float* ks, float* rows) {
     return stage_samples<KLDS>(a.kernel, a.S, ks, [&] {

@@ -78,7 +78,7 @@ __device__ __forceinline__ void light_add(const EvalLevel& L, const SampleTexel&
         hy = quotient(L.cy - ((float)h.y + 0.5f), L.f, rcf) * h.z;
         hz = -h.z;
     } else {
-        view_pos<false>(h.x, h.y, h.z, L.f, L.cx, L.cy, hx, hy, hz);
+        view_pos(h.x, h.y, h.z, L.f, L.cx, L.cy, hx, hy, hz);
     }
     const float vx = hx - T.px, vy = hy - T.py, vz = hz - T.pz;
     const float dd = ((vx * vx) + (vy * vy)) + (vz * vz);
@@ -126,7 +126,7 @@ __device__ __forceinline__ void light_group(const SsgiArgs& a, const EvalLevel& 
         if constexpr (FAST)
             project_fast(L, K, s + k, T, d[k], off, x, y);
         else
-            project_any(L, K, s + k, T, hit[k], d[k], off, x, y);
+            project_any<true>(L, K, s + k, T, hit[k], d[k], off, x, y);
         zs[k] = buf_f1(rz, off);
         xy[k] = __builtin_amdgcn_perm((unsigned)y, (unsigned)x, 0x05040100u);  // on screen both fit 16 bits
         __builtin_amdgcn_sched_barrier(0);
@@ -151,7 +151,13 @@ __device__ __forceinline__ void light_group(const SsgiArgs& a, const EvalLevel& 
     }
 }
 
-template <bool FAST, typename NT, typename CT, typename KP>
+// N samples at a time.  The general form (waves with a texel nearer than about
+// the sampling radius, focal lengths and radii outside fast_light's) takes the
+// group in the naive pass, one sample in multi-resolution launches, whose
+// registers its group of 4 would take: naive pass at 1280 x 720, 64 samples,
+// radius 40, 110 us with groups and 139 us without; frame at 2560 x 1440 154
+// and 145 us.
+template <bool FAST, int N, typename NT, typename CT, typename KP>
 __device__ __forceinline__ void ssgi_texel(const SsgiArgs& a, const EvalLevel& L, const SampleTexel& T, const Normal& n,
                                            KP K, float (&acc)[3]) {
     const Planes<NT> np(static_cast<const NT*>(a.c.normal), (unsigned)a.c.plane);
@@ -160,11 +166,9 @@ __device__ __forceinline__ void ssgi_texel(const SsgiArgs& a, const EvalLevel& L
     const float rmin = 0.1f * a.r;
     const float rmin2 = rmin * rmin;
     const float rcf = recip_fast(L.f);  // read in the fast form only
-    constexpr int N = FAST ? kLightGroup : 1;
     int s = 0;
     for (; s + N <= a.S; s += N) light_group<FAST, N>(a, L, T, n, K, s, rz, np, cp, rmin2, rcf, acc);
-    if constexpr (N > 1)
-        for (; s < a.S; ++s) light_group<FAST, 1>(a, L, T, n, K, s, rz, np, cp, rmin2, rcf, acc);
+    for (; N > 1 && s < a.S; ++s) light_group<FAST, 1>(a, L, T, n, K, s, rz, np, cp, rmin2, rcf, acc);
 }
 
 // one item (a listed texel, or a texel of a dense level)
@@ -186,9 +190,9 @@ __device__ __forceinline__ void ssgi_item(const SsgiArgs& a, const ItemMap& m, u
     if (valid_depth(z)) {
         const SampleTexel T = sample_texel(L, n, a.r, x, y, z);
         if (fast_samples(T, kmax, a.r) && fast_light(L, T, a.r))
-            ssgi_texel<true, NT, CT>(a, L, T, n, K, acc);
+            ssgi_texel<true, kLightGroup, NT, CT>(a, L, T, n, K, acc);
         else
-            ssgi_texel<false, NT, CT>(a, L, T, n, K, acc);
+            ssgi_texel<false, AL ? 1 : kLightGroup, NT, CT>(a, L, T, n, K, acc);
     }
     const float scale = (a.r * a.r) / (float)a.S;
     const unsigned o = L.compact ? local : (unsigned)y * (unsigned)L.W + (unsigned)x;
@@ -208,7 +212,7 @@ __device__ __forceinline__ void ssgi_items(const SsgiArgs& a, KP K, float kmax, 
 }
 
 // Per block: the blur's row sums (AL) and, KLDS, the samples in LDS; returns
-// the largest |component| of the samples (+inf when not staged).
+// the largest |component| of the samples.
 template <bool AL, bool KLDS>
 __device__ __forceinline__ float ssgi_stage(const SsgiArgs& a, float* ks, float* rows) {
     return stage_samples<KLDS>(a.kernel, a.S, ks, [&] {
