@@ -24,12 +24,9 @@ void k_ssgi(SsgiArgs a) {
         ssgi_items<NT, CT, AL>(a, a.kernel, kmax, (const float*)rows);
 }
 
-// Frames of a batch (see k_ssao_batch).  Four waves per SIMD: the frames'
-// gathers share the caches, and more waves lose more in them than they hide
-// (8 uneven frames, 64 samples: 904, 872, 899 and 922 us with 3, 4, 5 and 8
-// waves; a frame alone is fastest with all that fit).
+// frames of a batch (see k_ssao_batch)
 template <typename NT, typename CT, bool Q, bool KLDS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_ssgi_batch(const SsgiArgs* __restrict__ T, int n, unsigned* queue) {
+__global__ __launch_bounds__(256) void k_ssgi_batch(const SsgiArgs* __restrict__ T, int n, unsigned* queue) {
     __shared__ float ks[KLDS ? 3 * kLdsSamples : 1];
     __shared__ float rows[kRowLevels * kRowTable];
     __shared__ unsigned cbase[kMaxBatch + 1];
@@ -49,12 +46,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     });
 }
 
+// kSsgiBatchBlocks: the frames' gathers share the caches, and more blocks than
+// four per CU lose more in them than they hide, except where the batch is
+// small.  4 and 7 (all that fit) per CU, 64 samples, radius 2: 8 uneven frames
+// 947 and 1041 us, 24 uneven frames 1980 and 2259 us, two of 3840 x 2160 397
+// and 425 us, four of 1920 x 1080 245 and 241 us, 16 of 640 x 360 205 and 181
+// us.  mr_batch_tune times 8 (all), 6 and 2 as well.
+
 hipError_t launch_ssgi_batch(const SsgiArgs* T, int n, int S, int normal_dtype, int color_dtype,
                              unsigned total_hint, const BatchSchedule& bs, hipStream_t s) {
     const bool lds = S <= kLdsSamples;
+    const int per_cu = bs.blocks_per_cu ? bs.blocks_per_cu : kSsgiBatchBlocks;
 #define MR_GB(NT, CT, Q, KL)                                                                                   \
     hipLaunchKernelGGL((k_ssgi_batch<NT, CT, Q, KL>),                                                          \
-                       dim3(eval_blocks_capped<k_ssgi_batch<NT, CT, Q, KL>>(total_hint, bs.blocks_per_cu)), \
+                       dim3(eval_blocks_capped<k_ssgi_batch<NT, CT, Q, KL>>(total_hint, per_cu)), \
                        dim3(256), 0, s, T, n, bs.queue)
 #define MR_GBQ(NT, CT)                   \
     do {                                 \

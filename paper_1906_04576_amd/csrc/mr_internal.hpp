@@ -409,9 +409,11 @@ hipError_t launch_lean_masks_batch(const LeanArgs* T, const unsigned* blk_base, 
 constexpr int kQueueCounters = 8;  // work-queue counters: one per XCD
 // words zeroed by the batch's edge launch: the queue counters
 constexpr int kBatchCounters = kQueueCounters;
+// blocks per CU of an SSGI batch that names no number
+constexpr int kSsgiBatchBlocks = 4;
 struct BatchSchedule {
     bool queue_mode;    // per-XCD work queues instead of fixed strides
-    int blocks_per_cu;  // grid cap per CU, 0: as many blocks as are resident
+    int blocks_per_cu;  // grid cap per CU, 0: the launcher's (SSAO: as many blocks as are resident)
     unsigned* queue;    // kQueueCounters counters, zeroed by the edge launch
 };
 hipError_t launch_ssao_batch(const SsaoArgs* T, int n, int S, int normal_dtype, unsigned total_hint,
