@@ -11,8 +11,8 @@ namespace mr {
 // of 256, swept by a resident grid in fixed strides.  At most kTiledSamples
 // samples.  8 waves per SIMD (7 in LDS at H = 24, where a frame's list chunks
 // follow another's tiles, so that the row tables need LDS of their own): 24
-// uneven frames, halos 8, 16, 24, 904, 911, 916 us with 5 waves, now 872, 873
-// and 876 us.
+// uneven frames, halos 8, 16, 24, 904, 911, 916 us with 5 waves, now 870, 871
+// and 872 us.
 template <typename NT, int H>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(H == 24 ? 7 : 8)))
 void k_ssao_batch_tiled(const SsaoArgs* __restrict__ T, int n) {

@@ -17,12 +17,13 @@ struct DepthTile {
     unsigned x0, y0, tw;
 };
 
-// samples in flight together in the launches with depth tiles: their waves do
-// not wait for as many gathers, and groups of 8 (84 to 89 registers, 5 waves
-// per SIMD) left them behind the plane form.  Frame at 3840 x 2160 with 64
-// samples, halos 8, 16, 24: 123.1, 124.8, 125.7 us with groups of 8; 116.2,
-// 118.0, 118.1 us with groups of 4 and 8 waves per SIMD; groups of 2 within 1 %.
-constexpr int kTileGroup = 4;
+// Samples in flight together in the launches with depth tiles: kTileGroup of
+// the list levels' texels, kTilePair of a tile's, whose gathers mostly end in
+// LDS and which are not tested a group behind.  Frame at 3840 x 2160 with 64
+// samples, halos 8, 16, 24: 123.1, 124.8, 125.7 us with groups of 8 for both
+// (84 to 89 registers, 5 waves per SIMD); 116.2, 118.0, 118.1 us with groups
+// of 4 and 8 waves per SIMD; 115.4, 116.1, 115.7 us with the pairs.
+constexpr int kTileGroup = 4, kTilePair = 2;
 
 // gathers from a staged square of on-screen texels, else from the plane
 struct TileGather {
@@ -104,6 +105,32 @@ __device__ __forceinline__ int ssao_count(const SA& a, const EvalLevel& L, KP K,
     return occ;
 }
 
+// the same count of a tile's texel (fast form): kTilePair projections, then
+// their gathers, then their tests
+template <typename SA, typename KP>
+__device__ __forceinline__ int ssao_count_tile(const SA& a, const EvalLevel& L, KP K, const SampleTexel& T,
+                                               const TileGather& gather) {
+    int occ = 0, s = 0;
+    auto test = [&](auto count) {
+        constexpr int N = decltype(count)::value;
+        SampleGroup<N> g;
+        unsigned off[N];
+        int x[N], y[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            project_fast(L, K, s + k, T, g.d[k], off[k], x[k], y[k]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) g.zs[k] = gather(off[k], x[k], y[k]);
+        occ += __popc(test_samples(T, g, a.r, a.b, 0u));
+        s += N;
+    };
+    while (s + kTilePair <= a.S) test(std::integral_constant<int, kTilePair>{});
+    while (s < a.S) test(std::integral_constant<int, 1>{});
+    return occ;
+}
+
 // occlusion of one texel; K points to LDS (staged samples) or global memory;
 // kmax as in fast_samples; a holds the sampling parameters r, b and S
 // (SsaoArgs or SsaoSampling); dt: TILE, the staged square
@@ -113,15 +140,15 @@ __device__ __forceinline__ float ssao_texel(const SA& a, const EvalLevel& L, con
     const SampleTexel T = sample_texel(L, n, a.r, x, y, z);
     const unsigned last = last_texel(L);
     const __amdgpu_buffer_rsrc_t rz = buf_rsrc(L.z, last + 4u);
-    auto count = [&](const auto& gather) {
-        return fast_samples(T, kmax, a.r) ? ssao_count<true, N>(a, L, K, T, gather)
-                                        : ssao_count<false, N>(a, L, K, T, gather);
-    };
     int occ;
-    if constexpr (TILE)
-        occ = count(TileGather{rz, dt, last});
-    else
-        occ = count(PlaneGather{rz});
+    if constexpr (TILE) {
+        const TileGather gather{rz, dt, last};
+        occ = fast_samples(T, kmax, a.r) ? ssao_count_tile(a, L, K, T, gather) : ssao_count<false, N>(a, L, K, T, gather);
+    } else {
+        const PlaneGather gather{rz};
+        occ = fast_samples(T, kmax, a.r) ? ssao_count<true, N>(a, L, K, T, gather)
+                                         : ssao_count<false, N>(a, L, K, T, gather);
+    }
     return (float)occ / (float)a.S;
 }
 
