@@ -445,12 +445,14 @@ int do_build_masks(const mr_gbuffer* gb, const Geo& g, const mr_mask_params* mp,
         bl.H = g.Hi[i - 1];
         bl.r = r;
         bl.tiles_x = (unsigned)((bl.W + 255) / 256);
+        auto tiles_of = [&](int rows) { return bl.tiles_x * (unsigned)((bl.H + rows - 1) / rows); };
+        bl.rows = tiles_of(kBlurRowsBig) >= kBlurBigTiles ? kBlurRowsBig : kBlurRowsSmall;
         if (r > kBlurFusedMaxRadius) {
             if (launch_blur_wide(bl, s) != hipSuccess) return fail(MR_E_DEVICE, "blur kernel launch failed");
             continue;
         }
         bl.tile_base = tiles;
-        tiles += bl.tiles_x * (unsigned)((bl.H + kBlurTH - 1) / kBlurTH);
+        tiles += tiles_of(bl.rows);
         ba.lv[ba.nlev++] = bl;
     }
     ba.ntiles = tiles;

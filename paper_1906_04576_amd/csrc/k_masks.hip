@@ -367,7 +367,7 @@ hipError_t launch_edges(const EdgeArgs& a, int normal_dtype, hipStream_t s) {
 
 // ---------------------------------------------------------------------------
 // separable blur of every level below the coarsest in one launch.  A
-// workgroup owns 256 columns x kBlurTH rows of one level: the edge bytes of
+// workgroup owns 256 columns x BlurLevel.rows rows of one level: the edge bytes of
 // the tile plus its halo become one bit each in LDS (a ballot per 64 bytes),
 // then each thread walks down its column keeping the last 2r+1 horizontal
 // sums in a register shift ring, so every output needs one new horizontal
@@ -379,7 +379,7 @@ hipError_t launch_edges(const EdgeArgs& a, int normal_dtype, hipStream_t s) {
 // ---------------------------------------------------------------------------
 constexpr int kBlurTW = 256;
 constexpr int kBlurRowWords = (kBlurTW + 64) / 32;  // columns x0 - 32 .. x0 + 287
-constexpr int kBlurRows = kBlurTH + 2 * kMaxRadius;
+constexpr int kBlurRows = kBlurRowsBig + 2 * kMaxRadius;
 
 template <int R>
 __device__ __forceinline__ float hsum(const unsigned* row, const float* g) {
@@ -409,7 +409,7 @@ __device__ __forceinline__ void blur_columns(const BlurLevel& a, const unsigned 
 #pragma unroll
     for (int yy = 0; yy < 2 * R; ++yy) ring[yy + 1] = hsum<R>(eb[yy], g);
     const bool colok = X < W;
-    const int rows = min(kBlurTH, H - y0);
+    const int rows = min(a.rows, H - y0);
     for (int oy = 0; oy < rows; ++oy) {
 #pragma unroll
         for (int k = 0; k < 2 * R; ++k) ring[k] = ring[k + 1];
@@ -425,13 +425,13 @@ __device__ __forceinline__ void blur_columns(const BlurLevel& a, const unsigned 
     }
 }
 
-// The tile's edges as bits in LDS: rows y0 - r .. y0 + kBlurTH - 1 + r,
+// The tile's edges as bits in LDS: rows y0 - r .. y0 + a.rows - 1 + r,
 // columns x0 - 32 .. x0 + 287, 0 outside the image; the loads of kLoads
 // wave-wide pieces are in flight together.
 __device__ __forceinline__ void blur_stage(const BlurLevel& a, unsigned (*eb)[kBlurRowWords], int x0, int y0) {
     constexpr int kPieces = kBlurRowWords / 2, kLoads = 8;  // pieces of 64 columns per row
     const int W = a.W, H = a.H, lane = (int)__lane_id(), wave = (int)threadIdx.x >> 6;
-    const int n = (kBlurTH + 2 * a.r) * kPieces;
+    const int n = (a.rows + 2 * a.r) * kPieces;
     const __amdgpu_buffer_rsrc_t re = buf_rsrc(a.Ei, (unsigned)W * (unsigned)H);
     for (int i0 = wave; i0 < n; i0 += 4 * kLoads) {
         unsigned v[kLoads];
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(256) void k_blur(BlurArgs A) {
     const BlurLevel& a = A.lv[l];
     const unsigned tile = b - a.tile_base;
     const int x0 = (int)(tile % a.tiles_x) * kBlurTW;
-    const int y0 = (int)(tile / a.tiles_x) * kBlurTH;
+    const int y0 = (int)(tile / a.tiles_x) * a.rows;
     blur_stage(a, eb, x0, y0);
     const int r = a.r;
     switch (r) {
@@ -483,13 +483,13 @@ __global__ __launch_bounds__(256) void k_blur_wide(BlurLevel a) {
     __shared__ unsigned eb[kBlurRows][kBlurRowWords];
     const unsigned tile = xcd_remap(blockIdx.x, gridDim.x);
     const int x0 = (int)(tile % a.tiles_x) * kBlurTW;
-    const int y0 = (int)(tile / a.tiles_x) * kBlurTH;
+    const int y0 = (int)(tile / a.tiles_x) * a.rows;
     blur_stage(a, eb, x0, y0);
     blur_columns<R>(a, eb, x0, y0);
 }
 
 hipError_t launch_blur_wide(const BlurLevel& a, hipStream_t s) {
-    const unsigned n = a.tiles_x * (unsigned)((a.H + kBlurTH - 1) / kBlurTH);
+    const unsigned n = a.tiles_x * (unsigned)((a.H + a.rows - 1) / a.rows);
     switch (a.r) {
 #define MR_BLUR_WIDE(R) \
     case R: hipLaunchKernelGGL(k_blur_wide<R>, dim3(n), dim3(256), 0, s, a); break;

@@ -12,7 +12,6 @@ namespace mr {
 constexpr int kMaxLevels = MR_MAX_LEVELS;
 constexpr int kBlurFusedMaxRadiusC = 8;  // largest radius of the single-launch blur and the lean path
 constexpr int kMaxRadius = MR_MAX_RADIUS;
-constexpr int kBlurTH = 8;       // rows of a blur tile
 constexpr int kChunk = 4096;  // texels per compaction chunk (256 threads x 16)
 
 // ---------------------------------------------------------------------------
@@ -109,11 +108,20 @@ struct EdgeArgs {
     float fgx, fgy, fri2, fro2;
 };
 
+// Rows of a level's blur tiles: kBlurRowsBig (each row sum computed 1 + r / 16
+// times) where such tiles fill the chip, 256 CUs of 8 blocks each, else
+// kBlurRowsSmall (1 + r / 4 times, four times the blocks).  Masks with radii 3,
+// 5, 6: 16384 x 16384 2184 us with 8 rows and 1905 us with 32; 4096 x 4096 (2048
+// tiles of 32 rows) 155 and 144 us; 1366 x 768, radius 6, 26 and 33 us.
+constexpr int kBlurRowsSmall = 8, kBlurRowsBig = 32;
+constexpr unsigned kBlurBigTiles = 2048;
+
 struct BlurLevel {
     const uint8_t* Ei;
     float* a;
     uint8_t* S;
     int W, H, r;
+    int rows;  // of a tile
     unsigned tiles_x, tile_base;
     float g[2 * kMaxRadius + 1];
 };
