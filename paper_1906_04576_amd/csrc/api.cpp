@@ -484,18 +484,21 @@ int do_build_masks(const mr_gbuffer* gb, const Geo& g, const mr_mask_params* mp,
     }
     CompactArgs ca{};
     ca.nlev = g.nlev - 1;
-    unsigned cb = 0;
+    auto chunks_of = [&](int i) { return (unsigned)((g.n(i) + kChunk - 1) / kChunk); };
+    // the finest compacted level has the most chunks
+    ca.chunks = ca.nlev ? (chunks_of(g.levels[0]) + kCompactRuns - 1) / kCompactRuns : 1u;
+    unsigned rb = 0;
     for (int j = 0; j + 1 < g.nlev; ++j) {
         const int i = g.levels[j];
         ca.S[j] = m->stencil[i - 1];
         ca.list[j] = m->worklist[i - 1];
         ca.n[j] = (uint32_t)g.n(i);
-        ca.chunk_base[j] = cb;
+        ca.run_base[j] = rb;
         ca.count_idx[j] = i - 1;
-        cb += (unsigned)((g.n(i) + kChunk - 1) / kChunk);
+        rb += (chunks_of(i) + ca.chunks - 1) / ca.chunks;
     }
-    ca.chunk_base[ca.nlev] = cb;
-    ca.chunk_count = reinterpret_cast<uint32_t*>(base + sc.chunk_count_off);
+    ca.run_base[ca.nlev] = rb;
+    ca.run_count = reinterpret_cast<uint32_t*>(base + sc.chunk_count_off);
     ca.count = m->count;
     if (launch_compact(ca, m->level_map ? &la : nullptr, s) != hipSuccess) return fail(MR_E_DEVICE, "compaction kernel launch failed");
     return MR_OK;

@@ -3,17 +3,20 @@
 // list lengths left on the device.
 //
 // Two launches over the stencils of all compacted levels at once (a level's
-// stencil is cut into chunks of 4096 texels, 16 per thread):
-//   count   - nonzero bytes per chunk (popcount of a byte mask, block sum);
+// stencil is cut into runs of `chunks` chunks of 4096 texels, 16 per thread):
+//   count   - nonzero bytes per run (popcount of a byte mask, block sum);
 //             further blocks of the same launch write the owner-level map,
 //             which reads the same stencils;
-//   scatter - each chunk sums the counts of its level's earlier chunks (at
-//             most 65536 of them, 256 threads wide), recounts, takes a wave64
-//             prefix sum of the per-thread counts plus the wave totals from
-//             LDS, and writes its indices; a level's last chunk writes its
+//   scatter - each run's block sums the counts of its level's earlier runs,
+//             256 threads wide, and then chunk by chunk recounts, takes a
+//             wave64 prefix sum of the per-thread counts plus the wave totals
+//             from LDS, and writes its indices; a level's last run writes its
 //             total.
 // (The map, the count, a scan by one workgroup and the scatter were four
 // launches of 4 to 5 us each on a 1366 x 768 frame, most of it the launch.)
+// A run is one chunk up to kCompactRuns chunks in the finest level, then as
+// many as keep to that number: the sums over earlier runs grow with its
+// square.  TODO
 #include "mr_internal.hpp"
 
 namespace mr {
@@ -25,7 +28,7 @@ __device__ __forceinline__ unsigned nz_bytes(unsigned w) {
 
 __device__ __forceinline__ int find_level(const CompactArgs& a, unsigned c) {
     int l = 0;
-    while (l + 1 < a.nlev && c >= a.chunk_base[l + 1]) ++l;
+    while (l + 1 < a.nlev && c >= a.run_base[l + 1]) ++l;
     return l;
 }
 
@@ -47,19 +50,31 @@ __device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
     return v;
 }
 
-__device__ __forceinline__ void count_chunk(const CompactArgs& a, unsigned c, unsigned* wsum) {
-    const int l = find_level(a, c);
-    const unsigned off = (c - a.chunk_base[l]) * kChunk + threadIdx.x * 16;
-    unsigned cnt = 0;
-    if (off < a.n[l]) {
-        const uint4 v = load16(a.S[l], a.n[l], off);
-        cnt = nz_bytes(v.x) + nz_bytes(v.y) + nz_bytes(v.z) + nz_bytes(v.w);
+// 16 stencil bytes of the thread in chunk k of run c of level l, and where they
+// start
+struct Piece {
+    uint4 v;
+    unsigned off, cnt;
+};
+
+__device__ __forceinline__ Piece load_piece(const CompactArgs& a, int l, unsigned c, unsigned k) {
+    Piece p{make_uint4(0, 0, 0, 0), ((c - a.run_base[l]) * a.chunks + k) * kChunk + threadIdx.x * 16, 0u};
+    if (p.off < a.n[l]) {
+        p.v = load16(a.S[l], a.n[l], p.off);
+        p.cnt = nz_bytes(p.v.x) + nz_bytes(p.v.y) + nz_bytes(p.v.z) + nz_bytes(p.v.w);
     }
+    return p;
+}
+
+__device__ __forceinline__ void count_run(const CompactArgs& a, unsigned c, unsigned* wsum) {
+    const int l = find_level(a, c);
+    unsigned cnt = 0;
+    for (unsigned k = 0; k < a.chunks; ++k) cnt += load_piece(a, l, c, k).cnt;
     // wave reduction
     for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
     if (__lane_id() == 0) wsum[threadIdx.x >> 6] = cnt;
     __syncthreads();
-    if (threadIdx.x == 0) a.chunk_count[c] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    if (threadIdx.x == 0) a.run_count[c] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
 // owner-level map: the finest enabled level whose stencil covers the pixel;
@@ -81,67 +96,62 @@ __device__ __forceinline__ void map_chunk(const LevelMapArgs& a, unsigned c) {
     }
 }
 
-// blocks 0 .. nchunks - 1 count, the others write the level map
-__global__ __launch_bounds__(256) void k_count_map(CompactArgs a, LevelMapArgs m, unsigned nchunks) {
+// blocks 0 .. nruns - 1 count, the others write the level map
+__global__ __launch_bounds__(256) void k_count_map(CompactArgs a, LevelMapArgs m, unsigned nruns) {
     __shared__ unsigned wsum[4];
-    if (blockIdx.x < nchunks)
-        count_chunk(a, blockIdx.x, wsum);
+    if (blockIdx.x < nruns)
+        count_run(a, blockIdx.x, wsum);
     else
-        map_chunk(m, blockIdx.x - nchunks);
+        map_chunk(m, blockIdx.x - nruns);
 }
 
-__global__ __launch_bounds__(256) void k_scatter(CompactArgs a, unsigned nchunks) {
-    __shared__ unsigned wtot[4], wpre[4];
+__global__ __launch_bounds__(256) void k_scatter(CompactArgs a, unsigned nruns) {
+    __shared__ unsigned wtot[2][4], wpre[4];
     const unsigned c = blockIdx.x;
     if (c == 0 && threadIdx.x < kMaxLevels) {  // levels that are not compacted report 0
         bool listed = false;
         for (int l = 0; l < a.nlev; ++l) listed = listed || a.count_idx[l] == (int)threadIdx.x;
         if (!listed) a.count[threadIdx.x] = 0;
     }
-    if (c >= nchunks) return;
+    if (c >= nruns) return;
     const int l = find_level(a, c);
-    unsigned pre = 0;  // entries of the level's earlier chunks
-    for (unsigned u = a.chunk_base[l] + threadIdx.x; u < c; u += 256) pre += a.chunk_count[u];
+    unsigned pre = 0;  // entries of the level's earlier runs
+    for (unsigned u = a.run_base[l] + threadIdx.x; u < c; u += 256) pre += a.run_count[u];
     for (int d = 32; d >= 1; d >>= 1) pre += __shfl_xor(pre, d, 64);
-    const unsigned base = (c - a.chunk_base[l]) * kChunk;
-    const unsigned off = base + threadIdx.x * 16;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    unsigned cnt = 0;
-    if (off < a.n[l]) {
-        v = load16(a.S[l], a.n[l], off);
-        cnt = nz_bytes(v.x) + nz_bytes(v.y) + nz_bytes(v.z) + nz_bytes(v.w);
-    }
-    const unsigned inc = wave_incl_scan(cnt);
     const int wv = threadIdx.x >> 6;
-    if (__lane_id() == 63) {
-        wtot[wv] = inc;
-        wpre[wv] = pre;
-    }
-    __syncthreads();
-    unsigned before = wpre[0] + wpre[1] + wpre[2] + wpre[3];
-    if (threadIdx.x == 0 && c + 1u == a.chunk_base[l + 1])
-        a.count[a.count_idx[l]] = before + wtot[0] + wtot[1] + wtot[2] + wtot[3];
-    for (int w = 0; w < wv; ++w) before += wtot[w];
-    unsigned pos = before + inc - cnt;
-    if (!cnt) return;
+    if (__lane_id() == 63) wpre[wv] = pre;
     uint32_t* list = a.list[l];
-    const unsigned words[4] = {v.x, v.y, v.z, v.w};
+    unsigned done = 0;  // entries of the run's earlier chunks
+    for (unsigned k = 0; k < a.chunks; ++k) {
+        const Piece p = load_piece(a, l, c, k);
+        const unsigned inc = wave_incl_scan(p.cnt);
+        unsigned* tot = wtot[k & 1u];  // two sets: one barrier per chunk
+        if (__lane_id() == 63) tot[wv] = inc;
+        __syncthreads();
+        if (k == 0) done = wpre[0] + wpre[1] + wpre[2] + wpre[3];
+        unsigned pos = done + inc - p.cnt;
+        for (int w = 0; w < wv; ++w) pos += tot[w];
+        done += tot[0] + tot[1] + tot[2] + tot[3];
+        if (!p.cnt) continue;
+        const unsigned words[4] = {p.v.x, p.v.y, p.v.z, p.v.w};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const unsigned w = words[q];
+        for (int q = 0; q < 4; ++q) {
+            const unsigned w = words[q];
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-            if ((w >> (8 * b)) & 0xFFu) list[pos++] = off + 4 * q + b;
+            for (int b = 0; b < 4; ++b)
+                if ((w >> (8 * b)) & 0xFFu) list[pos++] = p.off + 4 * q + b;
+        }
     }
+    if (threadIdx.x == 0 && c + 1u == a.run_base[l + 1]) a.count[a.count_idx[l]] = done;
 }
 
 hipError_t launch_compact(const CompactArgs& a, const LevelMapArgs* map, hipStream_t s) {
-    const unsigned nchunks = a.chunk_base[a.nlev];
+    const unsigned nruns = a.run_base[a.nlev];
     unsigned maps = 0;
     if (map) maps = ((unsigned)map->W * (unsigned)map->H + kMapPixels - 1u) / kMapPixels;
-    if (nchunks + maps)
-        hipLaunchKernelGGL(k_count_map, dim3(nchunks + maps), dim3(256), 0, s, a, map ? *map : LevelMapArgs{}, nchunks);
-    hipLaunchKernelGGL(k_scatter, dim3(nchunks ? nchunks : 1u), dim3(256), 0, s, a, nchunks);
+    if (nruns + maps)
+        hipLaunchKernelGGL(k_count_map, dim3(nruns + maps), dim3(256), 0, s, a, map ? *map : LevelMapArgs{}, nruns);
+    hipLaunchKernelGGL(k_scatter, dim3(nruns ? nruns : 1u), dim3(256), 0, s, a, nruns);
     return hipGetLastError();
 }
 

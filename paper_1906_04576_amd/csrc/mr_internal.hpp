@@ -13,6 +13,7 @@ constexpr int kMaxLevels = MR_MAX_LEVELS;
 constexpr int kBlurFusedMaxRadiusC = 8;  // largest radius of the single-launch blur and the lean path
 constexpr int kMaxRadius = MR_MAX_RADIUS;
 constexpr int kChunk = 4096;  // texels per compaction chunk (256 threads x 16)
+constexpr unsigned kCompactRuns = 4096;  // runs of a compacted level at most
 
 // ---------------------------------------------------------------------------
 // device helpers
@@ -151,10 +152,11 @@ struct CompactArgs {
     const uint8_t* S[kMaxLevels];
     uint32_t* list[kMaxLevels];
     uint32_t n[kMaxLevels];          // texels per compacted level
-    uint32_t chunk_base[kMaxLevels + 1];
+    uint32_t run_base[kMaxLevels + 1];  // first run of each level
+    uint32_t chunks;                 // chunks of a run
     int count_idx[kMaxLevels];       // index into count[] per compacted level
     int nlev;                        // compacted levels
-    uint32_t* chunk_count;           // [total chunks]
+    uint32_t* run_count;             // [total runs]
     uint32_t* count;                 // [MR_MAX_LEVELS]
 };
 
