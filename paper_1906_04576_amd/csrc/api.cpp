@@ -328,14 +328,14 @@ bool lean_ok(const Geo& g, const mr_mask_params* mp) {
 // The compact layout in two parts.  The mask pyramid (counts, tile totals,
 // edge and stencil bits, ranks, work lists and point-sampled level depth)
 // depends only on the frame's inputs; the scratch part (a_i and sub-image
-// values by rank, the coarsest level, hard-shadow bits, blurred values) is
-// rewritten by every frame.  Offsets of the pyramid fields are from the
+// values by rank, the coarsest level, blurred values) is rewritten by every
+// frame.  Offsets of the pyramid fields are from the
 // pyramid's base, those of the scratch fields from the scratch's base;
 // mr_frame places the scratch right after the pyramid.
 struct LeanLayout {
     size_t count = 0, tot = 0, Eb[3] = {}, Sb[3] = {}, woff[3] = {}, list[3] = {}, zi[kMaxLevels] = {};
     size_t pyramid = 0;  // bytes of the pyramid part
-    size_t ac[3] = {}, cc[3] = {}, cL = 0, hard = 0;
+    size_t ac[3] = {}, cc[3] = {}, cL = 0;
     size_t bc[3] = {}, bL = 0;  // SSAO: bilaterally blurred values
     size_t scratch = 0;  // bytes of the scratch part
     unsigned nblk = 0;
@@ -376,7 +376,6 @@ LeanLayout lean_layout(const Geo& g, int effect) {
         f.cc[i - 1] = take(4 * n * C);
     }
     f.cL = take(4 * (size_t)g.n(g.L) * C);
-    if (effect == MR_EFFECT_SHADOW) f.hard = take((size_t)g.W * g.H);
     if (effect == MR_EFFECT_SSAO) {
         for (int j = 0; j + 1 < g.nlev; ++j) {
             const int i = g.levels[j];
@@ -766,7 +765,6 @@ void build_lean(const mr_frame_desc* d, const Geo& g, const void* params, uint8_
     const LeanLayout f = lean_layout(g, effect);
     uint8_t* const b = pyr;
     uint32_t* count = reinterpret_cast<uint32_t*>(b + f.count);
-    const uint8_t* hard = nullptr;
     if (effect == MR_EFFECT_SHADOW) {
         HardArgs& ha = P.ha;
         ha.depth = d->g.depth;
@@ -778,15 +776,12 @@ void build_lean(const mr_frame_desc* d, const Geo& g, const void* params, uint8_
         memcpy(ha.M, d->shadow->view_to_light, sizeof(ha.M));
         ha.fL = d->shadow->light_focal_px;
         ha.bias = d->shadow->bias;
-        ha.hard = scr + f.hard;
         P.has_hard = true;
-        hard = scr + f.hard;
     }
     // edges as bits, point-sampled level depth
     EdgeArgs& ea = P.ea;
     ea.depth = d->g.depth;
     ea.normal = d->g.normal;
-    ea.hard = hard;
     ea.W = g.W;
     ea.H = g.H;
     ea.depth_ratio = d->mp.depth_ratio;
@@ -1145,8 +1140,8 @@ int run_plan(const BatchPlan& P, hipStream_t s) {
     const int et = c.edge_tile;
     const bool wide = et == 0 && P.wide_ok;
     if (!P.cached) {
-        if (launch_edges_batch(P.te, P.edge_base[et], P.edge_tx[et], P.n, P.edge_total[et], P.ndt, false, wide,
-                               P.queue, s) != hipSuccess)
+        if (launch_edges_batch(P.te, P.edge_base[et], P.edge_tx[et], P.n, P.edge_total[et], P.ndt, wide, P.queue,
+                               s) != hipSuccess)
             return fail(MR_E_DEVICE, "batched edge kernel launch failed");
         if (launch_lean_masks_batch(P.tl, P.rank_base, P.n, P.rank_total, s) != hipSuccess)
             return fail(MR_E_DEVICE, "batched rank kernel launch failed");

@@ -272,7 +272,8 @@ hipError_t launch_edges_shadow(const EdgeArgs& a, const HardArgs& ha, int normal
 // them (here and in the other batch kernels) lets the compiler keep a frame's
 // fields in registers across the kernel's own stores instead of loading them
 // again after each (the batch edge kernel ran 18 % faster with it).
-template <typename NT, bool HARD, bool BITS, bool WIDE>
+// (Compact frame path: bit-packed edges, widths divisible by 4, no shadow bits.)
+template <typename NT, bool WIDE>
 __global__ __launch_bounds__(256) void k_edges_batch(const EdgeArgs* __restrict__ T,
                                                      const unsigned* __restrict__ tile_base,
                                                      const unsigned* __restrict__ tiles_x, int n, unsigned* queue) {
@@ -281,27 +282,20 @@ __global__ __launch_bounds__(256) void k_edges_batch(const EdgeArgs* __restrict_
     int f = 0;
     for (int k = 1; k < n; ++k) f += g >= tile_base[k] ? 1 : 0;
     const unsigned local = g - tile_base[f];
-    edges_tile<NT, HARD, BITS, WIDE>(T[f], local, tiles_x[f]);
+    edges_tile<NT, false, true, WIDE>(T[f], local, tiles_x[f]);
 }
 
 hipError_t launch_edges_batch(const EdgeArgs* T, const unsigned* tile_base, const unsigned* tiles_x, int n,
-                              unsigned total, int normal_dtype, bool hard, bool wide, unsigned* queue,
-                              hipStream_t s) {
-    // compact frame path only: bit-packed edges (BITS) and widths divisible by 4
-#define MR_EB(NT, HD, WD)                                                                                  \
-    hipLaunchKernelGGL((k_edges_batch<NT, HD, true, WD>), dim3(total), dim3(256), 0, s, T, tile_base, tiles_x, n, \
-                       queue)
+                              unsigned total, int normal_dtype, bool wide, unsigned* queue, hipStream_t s) {
+#define MR_EB(NT, WD) \
+    hipLaunchKernelGGL((k_edges_batch<NT, WD>), dim3(total), dim3(256), 0, s, T, tile_base, tiles_x, n, queue)
     const bool f16 = normal_dtype == MR_F16;
     if (wide) {
-        if (f16 && hard) MR_EB(_Float16, true, true);
-        else if (f16) MR_EB(_Float16, false, true);
-        else if (hard) MR_EB(float, true, true);
-        else MR_EB(float, false, true);
+        if (f16) MR_EB(_Float16, true);
+        else MR_EB(float, true);
     } else {
-        if (f16 && hard) MR_EB(_Float16, true, false);
-        else if (f16) MR_EB(_Float16, false, false);
-        else if (hard) MR_EB(float, true, false);
-        else MR_EB(float, false, false);
+        if (f16) MR_EB(_Float16, false);
+        else MR_EB(float, false);
     }
 #undef MR_EB
     return hipGetLastError();
@@ -336,10 +330,9 @@ hipError_t launch_edges(const EdgeArgs& a, int normal_dtype, hipStream_t s) {
         else                                                                                                 \
             hipLaunchKernelGGL((k_edges_vec<NT, HD, BT, false>), dim3(n), dim3(256), 0, s, a, tx, n);        \
     } while (0)
-        if (bits) {
-            if (f16 && hard) MR_EDGES(_Float16, true, true);
-            else if (f16) MR_EDGES(_Float16, false, true);
-            else if (hard) MR_EDGES(float, true, true);
+        if (bits) {  // (with shadow bits: launch_edges_shadow)
+            if (hard) return hipErrorInvalidValue;
+            if (f16) MR_EDGES(_Float16, false, true);
             else MR_EDGES(float, false, true);
         } else {
             if (f16 && hard) MR_EDGES(_Float16, true, false);

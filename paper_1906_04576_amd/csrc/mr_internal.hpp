@@ -234,7 +234,7 @@ struct HardArgs {
     int size;
     float M[12];
     float fL, bias;
-    uint8_t* hard;
+    uint8_t* hard;  // (null in the frames' edge tiles, which store no bits)
 };
 
 struct MergeLevel {
@@ -411,8 +411,7 @@ void edges_tiles(int W, int H, bool wide, unsigned& tiles_x, unsigned& ntiles);
 // batched frames: argument tables in device memory, one launch per stage.
 // The edge launch also zeroes `queue` (the evaluation's per-XCD counters).
 hipError_t launch_edges_batch(const EdgeArgs* T, const unsigned* tile_base, const unsigned* tiles_x, int n,
-                              unsigned total, int normal_dtype, bool hard, bool wide, unsigned* queue,
-                              hipStream_t s);
+                              unsigned total, int normal_dtype, bool wide, unsigned* queue, hipStream_t s);
 hipError_t launch_lean_masks_batch(const LeanArgs* T, const unsigned* blk_base, int n, unsigned total,
                                    hipStream_t s);
 // how a batched evaluation hands out its chunks

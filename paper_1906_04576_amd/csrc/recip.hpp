@@ -46,12 +46,11 @@ __device__ __forceinline__ float quotient(float n, float d, float rc) {
     return __builtin_fmaf(__builtin_fmaf(-d, q, n), rc, q);
 }
 
-// 1.0f / sqrtf(x) (both rounded) for kRsqrtLo <= x < kRsqrtHi: Goldschmidt's
+// 1.0f / sqrtf(x) (both rounded) for 2^-90 <= x < 2^90: Goldschmidt's
 // iteration for the square root g with h = 1/(2 g) beside it, the residual
 // x - g g exact in a fused multiply-add, then recip_fast.  The two IEEE
 // operations take 19 instructions, these 11.  tests/native/rsqrt_check.hip
 // compares them for every float of the range.
-constexpr float kRsqrtLo = 0x1p-90f, kRsqrtHi = 0x1p90f;
 __device__ __forceinline__ float rsqrt_fast(float x) {
     const float y = __builtin_amdgcn_rsqf(x);
     float g = x * y, h = 0.5f * y;
