@@ -13,7 +13,7 @@ BIN = os.path.join(HERE, "_bin")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-PROGRAMS = ["recip_check", "rsqrt_check"]
+PROGRAMS = ["recip_check", "rsqrt_check", "quotient_check"]
 # C clients of the library (gcc, linked against libmr.so and the HIP runtime)
 C_PROGRAMS = ["abi_frame"]
 ROOT = os.path.dirname(os.path.dirname(HERE))
