@@ -495,8 +495,9 @@ MR_API int mr_batch_setup_cached(const mr_frame_desc* frames, void* const* pyram
  *                          chunks of its XCD's share of the item space;
  *                          1: the blocks of an XCD take chunks one at a time
  *                          from a counter in the workspace
- *   eval_blocks_per_cu  cap on evaluation blocks per CU, 0..64; 0: 4 for
- *                       SSGI, as many as can be resident for SSAO
+ *   eval_blocks_per_cu  cap on evaluation blocks per CU, 0..64; 0: for SSGI
+ *                       4 (6 with at most 16 samples), for SSAO as many as
+ *                       can be resident
  *   merge_generic       0: a merge with fixed tap geometry where one applies
  *                          (the levels 1, 2, 3, 4 or 1, 3, 4 enabled),
  *                       1: the general merge

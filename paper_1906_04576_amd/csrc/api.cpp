@@ -1867,7 +1867,7 @@ int mr_batch_tune(void* plan, int reps, mr_batch_config* best, void* stream) {
     const mr_batch_config base = bc;
     // (as many blocks per CU as 0 stands for are not timed again: 8 blocks of
     // four waves fill a CU, which SSAO's batches do)
-    const int same_as_0 = P.effect == MR_EFFECT_SSGI ? kSsgiBatchBlocks : 8;
+    const int same_as_0 = P.effect == MR_EFFECT_SSGI ? ssgi_batch_blocks(P.S) : 8;
     for (int q = 0; q < 2; ++q)
         for (int bpc : {0, 8, 6, 4, 2}) {
             if (bpc == same_as_0) continue;

@@ -46,17 +46,10 @@ __global__ __launch_bounds__(256) void k_ssgi_batch(const SsgiArgs* __restrict__
     });
 }
 
-// kSsgiBatchBlocks: the frames' gathers share the caches, and more blocks than
-// four per CU lose more in them than they hide, except where the batch is
-// small.  4 and 7 (all that fit) per CU, 64 samples, radius 2: 8 uneven frames
-// 947 and 1041 us, 24 uneven frames 1980 and 2259 us, two of 3840 x 2160 397
-// and 425 us, four of 1920 x 1080 245 and 241 us, 16 of 640 x 360 205 and 181
-// us.  mr_batch_tune times 8 (all), 6 and 2 as well.
-
 hipError_t launch_ssgi_batch(const SsgiArgs* T, int n, int S, int normal_dtype, int color_dtype,
                              unsigned total_hint, const BatchSchedule& bs, hipStream_t s) {
     const bool lds = S <= kLdsSamples;
-    const int per_cu = bs.blocks_per_cu ? bs.blocks_per_cu : kSsgiBatchBlocks;
+    const int per_cu = bs.blocks_per_cu ? bs.blocks_per_cu : ssgi_batch_blocks(S);
 #define MR_GB(NT, CT, Q, KL)                                                                                   \
     hipLaunchKernelGGL((k_ssgi_batch<NT, CT, Q, KL>),                                                          \
                        dim3(eval_blocks_capped<k_ssgi_batch<NT, CT, Q, KL>>(total_hint, per_cu)), \

@@ -418,8 +418,15 @@ hipError_t launch_lean_masks_batch(const LeanArgs* T, const unsigned* blk_base, 
 constexpr int kQueueCounters = 8;  // work-queue counters: one per XCD
 // words zeroed by the batch's edge launch: the queue counters
 constexpr int kBatchCounters = kQueueCounters;
-// blocks per CU of an SSGI batch that names no number
-constexpr int kSsgiBatchBlocks = 4;
+// Blocks per CU of an SSGI batch of S samples that names no number.  The light's
+// gathers share the caches, and more blocks lose more in them than they hide,
+// the more so the farther and the more the samples reach.  4, 6 and 7 (all
+// that fit) per CU: 24 uneven frames, 64 samples, radius 1: 1625, 1497, 1649
+// us, radius 2: 1984, 2141, 2261 us, radius 4: 2818, 3046, 3227 us; four of
+// 1920 x 1080, radius 2: 245, 250, 242 us; 16 of 640 x 360, 8 samples, 85, 81,
+// 83 us.  The radius is in the scene's units, so only the samples decide;
+// mr_batch_tune times the others.
+constexpr int ssgi_batch_blocks(int S) { return S <= 16 ? 6 : 4; }
 struct BatchSchedule {
     bool queue_mode;    // per-XCD work queues instead of fixed strides
     int blocks_per_cu;  // grid cap per CU, 0: the launcher's (SSAO: as many blocks as are resident)
