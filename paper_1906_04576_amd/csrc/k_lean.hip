@@ -79,9 +79,11 @@ hipError_t launch_lean_level_map(const LeanMapArgs& a, hipStream_t s) {
 // move the allocator above it: its occupancy is fixed at 5 (measured faster
 // than 4 waves without the few spilled registers).
 constexpr int merge_waves(int C) { return C == 1 ? 1 : 5; }
-// The merge of fixed levels needs 82 for three channels and fits 80 (6 waves:
-// 135 us for the batch of eight, 140 us at 5).
-constexpr int merge4_waves(int C) { return C == 1 ? 1 : 6; }
+// The merge of fixed levels needs 82 for three channels.  Batches fit it into
+// 80 (6 waves: 8 uneven frames of 4 samples 290 us, 298 us at 5); a frame alone
+// is faster without the squeeze (3840 x 2160 80.4 us, 82.1 us at 6; 2560 x 1440
+// 49.8 and 50.0 us).
+constexpr int merge4_batch_waves(int C) { return C == 1 ? 1 : 6; }
 
 template <int C, typename VT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(merge_waves(C))))
@@ -95,8 +97,7 @@ void k_lean_merge(LeanMergeArgs a, unsigned tiles_x, unsigned ntiles) {
 
 // L2 false: the levels 1, 3 and 4
 template <int C, typename VT, bool L2>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(merge4_waves(C))))
-void k_lean_merge4(LeanMergeArgs a, unsigned tiles_x, unsigned ntiles) {
+__global__ __launch_bounds__(256) void k_lean_merge4(LeanMergeArgs a, unsigned tiles_x, unsigned ntiles) {
     __shared__ Merge4Lds<C> sm;
     merge4_tile<C, VT, L2>(a, xcd_remap(blockIdx.x, ntiles), tiles_x, sm);
 }
@@ -104,7 +105,7 @@ void k_lean_merge4(LeanMergeArgs a, unsigned tiles_x, unsigned ntiles) {
 // frames of a batch: tile_base[f] = first merge tile of frame f; GEO one of
 // kMergeGeneral, kMerge1234, kMerge134
 template <int C, typename VT, int GEO>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GEO != kMergeGeneral ? merge4_waves(C) : merge_waves(C))))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(GEO != kMergeGeneral ? merge4_batch_waves(C) : merge_waves(C))))
 void k_lean_merge_batch(const LeanMergeArgs* __restrict__ T, const unsigned* __restrict__ tile_base,
                         const unsigned* __restrict__ tiles_x, int n) {
     const unsigned g = xcd_remap(blockIdx.x, gridDim.x);
