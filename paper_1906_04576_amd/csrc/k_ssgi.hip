@@ -5,16 +5,9 @@
 namespace mr {
 
 // KLDS: the samples are staged in LDS (S <= kLdsSamples), else read from
-// global memory; one instance each keeps the sample loop inlined once.
-// AL: five waves per SIMD at a time, of the seven that the registers (and the
-// grid) allow: the light's gathers share the caches, and the blocks above five
-// per CU refill the slots that fall free.  3840 x 2160, 64 samples, radius 1,
-// 2, 4, 16: 163, 211, 320, 349 us with seven at a time, 166, 204, 309, 336 us
-// with five (168, 211, 313, 358 us with a grid of five per CU as well); the
-// same within 1 % at 2560 x 1440 and below, where four cost 10 %.
+// global memory; one instance each keeps the sample loop inlined once
 template <typename NT, typename CT, bool AL, bool KLDS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, AL ? 5 : 8)))
-void k_ssgi(SsgiArgs a) {
+__global__ __launch_bounds__(256) void k_ssgi(SsgiArgs a) {
     __shared__ float ks[KLDS ? 3 * kLdsSamples : 1];
     __shared__ float rows[kRowLevels * kRowTable];
     const float kmax = ssgi_stage<AL, KLDS>(a, ks, rows);
