@@ -57,8 +57,8 @@ struct Piece {
     unsigned off, cnt;
 };
 
-__device__ __forceinline__ Piece load_piece(const CompactArgs& a, int l, unsigned c, unsigned k) {
-    Piece p{make_uint4(0, 0, 0, 0), ((c - a.run_base[l]) * a.chunks + k) * kChunk + threadIdx.x * 16, 0u};
+__device__ __forceinline__ Piece load_piece(const CompactArgs& a, int l, unsigned c, unsigned chunks, unsigned k) {
+    Piece p{make_uint4(0, 0, 0, 0), ((c - a.run_base[l]) * chunks + k) * kChunk + threadIdx.x * 16, 0u};
     if (p.off < a.n[l]) {
         p.v = load16(a.S[l], a.n[l], p.off);
         p.cnt = nz_bytes(p.v.x) + nz_bytes(p.v.y) + nz_bytes(p.v.z) + nz_bytes(p.v.w);
@@ -66,10 +66,12 @@ __device__ __forceinline__ Piece load_piece(const CompactArgs& a, int l, unsigne
     return p;
 }
 
+template <bool ONE>
 __device__ __forceinline__ void count_run(const CompactArgs& a, unsigned c, unsigned* wsum) {
+    const unsigned chunks = ONE ? 1u : a.chunks;
     const int l = find_level(a, c);
     unsigned cnt = 0;
-    for (unsigned k = 0; k < a.chunks; ++k) cnt += load_piece(a, l, c, k).cnt;
+    for (unsigned k = 0; k < chunks; ++k) cnt += load_piece(a, l, c, chunks, k).cnt;
     // wave reduction
     for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
     if (__lane_id() == 0) wsum[threadIdx.x >> 6] = cnt;
@@ -96,15 +98,19 @@ __device__ __forceinline__ void map_chunk(const LevelMapArgs& a, unsigned c) {
     }
 }
 
-// blocks 0 .. nruns - 1 count, the others write the level map
+// blocks 0 .. nruns - 1 count, the others write the level map.  ONE: runs of one
+// chunk, without the loops (3840 x 2160: count 4.9 and 5.1 us, scatter 7.7 and
+// 8.3 us).
+template <bool ONE>
 __global__ __launch_bounds__(256) void k_count_map(CompactArgs a, LevelMapArgs m, unsigned nruns) {
     __shared__ unsigned wsum[4];
     if (blockIdx.x < nruns)
-        count_run(a, blockIdx.x, wsum);
+        count_run<ONE>(a, blockIdx.x, wsum);
     else
         map_chunk(m, blockIdx.x - nruns);
 }
 
+template <bool ONE>
 __global__ __launch_bounds__(256) void k_scatter(CompactArgs a, unsigned nruns) {
     __shared__ unsigned wtot[2][4], wpre[4];
     const unsigned c = blockIdx.x;
@@ -120,10 +126,11 @@ __global__ __launch_bounds__(256) void k_scatter(CompactArgs a, unsigned nruns) 
     for (int d = 32; d >= 1; d >>= 1) pre += __shfl_xor(pre, d, 64);
     const int wv = threadIdx.x >> 6;
     if (__lane_id() == 63) wpre[wv] = pre;
+    const unsigned chunks = ONE ? 1u : a.chunks;
     uint32_t* list = a.list[l];
     unsigned done = 0;  // entries of the run's earlier chunks
-    for (unsigned k = 0; k < a.chunks; ++k) {
-        const Piece p = load_piece(a, l, c, k);
+    for (unsigned k = 0; k < chunks; ++k) {
+        const Piece p = load_piece(a, l, c, chunks, k);
         const unsigned inc = wave_incl_scan(p.cnt);
         unsigned* tot = wtot[k & 1u];  // two sets: one barrier per chunk
         if (__lane_id() == 63) tot[wv] = inc;
@@ -149,9 +156,15 @@ hipError_t launch_compact(const CompactArgs& a, const LevelMapArgs* map, hipStre
     const unsigned nruns = a.run_base[a.nlev];
     unsigned maps = 0;
     if (map) maps = ((unsigned)map->W * (unsigned)map->H + kMapPixels - 1u) / kMapPixels;
-    if (nruns + maps)
-        hipLaunchKernelGGL(k_count_map, dim3(nruns + maps), dim3(256), 0, s, a, map ? *map : LevelMapArgs{}, nruns);
-    hipLaunchKernelGGL(k_scatter, dim3(nruns ? nruns : 1u), dim3(256), 0, s, a, nruns);
+    const LevelMapArgs m = map ? *map : LevelMapArgs{};
+    const dim3 count(nruns + maps), scatter(nruns ? nruns : 1u), threads(256);
+    if (a.chunks == 1u) {
+        if (nruns + maps) hipLaunchKernelGGL(k_count_map<true>, count, threads, 0, s, a, m, nruns);
+        hipLaunchKernelGGL(k_scatter<true>, scatter, threads, 0, s, a, nruns);
+    } else {
+        if (nruns + maps) hipLaunchKernelGGL(k_count_map<false>, count, threads, 0, s, a, m, nruns);
+        hipLaunchKernelGGL(k_scatter<false>, scatter, threads, 0, s, a, nruns);
+    }
     return hipGetLastError();
 }
 
