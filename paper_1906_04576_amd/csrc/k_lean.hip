@@ -80,10 +80,12 @@ hipError_t launch_lean_level_map(const LeanMapArgs& a, hipStream_t s) {
 // than 4 waves without the few spilled registers).
 constexpr int merge_waves(int C) { return C == 1 ? 1 : 5; }
 // The merge of fixed levels needs 82 for three channels.  Batches fit it into
-// 80 (6 waves: 8 uneven frames of 4 samples 290 us, 298 us at 5); a frame alone
-// is faster without the squeeze (3840 x 2160 80.4 us, 82.1 us at 6; 2560 x 1440
-// 49.8 and 50.0 us).
+// 80 (6 waves: 8 uneven frames of 4 samples 290 us, 298 us at 5).  So do frames
+// with level 2 (4 samples: 3840 x 2160 92.8 us, 93.4 us at 5; 7680 x 4320 338
+// and 347 us); without it they are faster unsqueezed (83.3 us at 6, 82.6 us;
+// 292 and 288 us; the same order from 1920 x 1080 on).
 constexpr int merge4_batch_waves(int C) { return C == 1 ? 1 : 6; }
+constexpr int merge4_waves(int C, bool l2) { return C == 1 || !l2 ? 1 : 6; }
 
 template <int C, typename VT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(merge_waves(C))))
@@ -97,7 +99,8 @@ void k_lean_merge(LeanMergeArgs a, unsigned tiles_x, unsigned ntiles) {
 
 // L2 false: the levels 1, 3 and 4
 template <int C, typename VT, bool L2>
-__global__ __launch_bounds__(256) void k_lean_merge4(LeanMergeArgs a, unsigned tiles_x, unsigned ntiles) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(merge4_waves(C, L2))))
+void k_lean_merge4(LeanMergeArgs a, unsigned tiles_x, unsigned ntiles) {
     __shared__ Merge4Lds<C> sm;
     merge4_tile<C, VT, L2>(a, xcd_remap(blockIdx.x, ntiles), tiles_x, sm);
 }
