@@ -99,12 +99,23 @@ __device__ __forceinline__ ChunkRange chunk_range(unsigned nchunks) {
 // hands a new chunk to whichever wave slots fall free.  (A resident grid with
 // an equal number of chunks per block ended unevenly: the SIMDs favour their
 // oldest waves, and the last blocks ran for a third of the launch with their
-// neighbours' slots empty.)
-__host__ __device__ __forceinline__ bool one_dense_level(const EvalCommon& c) { return c.nlev == 1 && !c.lv[0].list; }
+// neighbours' slots empty.)  With fewer than kNaiveSamples samples a block's
+// work is too short for that: its set-up, once per 256 texels, costs more, and
+// a resident grid takes the chunks.  3840 x 2160, a block per chunk and a
+// resident grid: SSGI, 1 sample 74.7 and 58.1 us, 6 samples 117 and 111 us, 8
+// samples 127 and 127 us; SSAO, 1 sample 58 and 46 us, 6 samples 83.8 and 83.1
+// us, 8 samples 88 and 98 us.
+constexpr int kNaiveSamples = 8;
+__host__ inline bool one_dense_level(const EvalCommon& c) { return c.nlev == 1 && !c.lv[0].list; }
 
 __device__ __forceinline__ ChunkRange naive_chunk(unsigned nchunks) {
     const unsigned b = xcd_remap(blockIdx.x, gridDim.x);
     return {b, min(nchunks, b + 1u), 1u};
+}
+
+// the chunks of a block: one where the grid has a block for each
+__device__ __forceinline__ ChunkRange level_chunks(unsigned nchunks) {
+    return gridDim.x == nchunks ? naive_chunk(nchunks) : chunk_range(nchunks);
 }
 
 // Chunks of a launch's item space handed to its blocks.  Q false: each block
@@ -353,10 +364,12 @@ __host__ inline unsigned eval_blocks(unsigned total_hint) {
     return b;
 }
 
-// grid of an evaluation pass: one block per chunk of a naive pass
+// grid of an evaluation pass: one block per chunk of a naive pass (of at least
+// kNaiveSamples samples)
 template <auto Kernel>
-__host__ inline unsigned eval_grid(const EvalCommon& c, unsigned total_hint) {
-    return one_dense_level(c) ? (c.lv[0].dense_n + 255u) / 256u : eval_blocks<Kernel>(total_hint);
+__host__ inline unsigned eval_grid(const EvalCommon& c, unsigned total_hint, int samples) {
+    return one_dense_level(c) && samples >= kNaiveSamples ? (c.lv[0].dense_n + 255u) / 256u
+                                                          : eval_blocks<Kernel>(total_hint);
 }
 
 // compute units of the current device, queried once per device

@@ -242,7 +242,7 @@ hipError_t launch_ssao(const SsaoArgs& a, int normal_dtype, unsigned total_hint,
         return hipGetLastError();
     }
 #define MR_SSAO(NT, AL, KL) \
-    hipLaunchKernelGGL((k_ssao<NT, AL, KL>), dim3(eval_grid<k_ssao<NT, AL, KL>>(a.c, total_hint)), dim3(256), 0, s, a)
+    hipLaunchKernelGGL((k_ssao<NT, AL, KL>), dim3(eval_grid<k_ssao<NT, AL, KL>>(a.c, total_hint, a.S)), dim3(256), 0, s, a)
     if (normal_dtype == MR_F16) {
         if (al) {
             if (lds) MR_SSAO(_Float16, true, true);

@@ -78,7 +78,7 @@ hipError_t launch_ssgi(const SsgiArgs& a, int normal_dtype, int color_dtype, uns
                        hipStream_t s) {
     const bool al = fused_alpha(a.c), lds = a.S <= kLdsSamples;
 #define MR_SK(NT, CT, AL, KL) \
-    hipLaunchKernelGGL((k_ssgi<NT, CT, AL, KL>), dim3(eval_grid<k_ssgi<NT, CT, AL, KL>>(a.c, total_hint)), dim3(256), 0, s, a)
+    hipLaunchKernelGGL((k_ssgi<NT, CT, AL, KL>), dim3(eval_grid<k_ssgi<NT, CT, AL, KL>>(a.c, total_hint, a.S)), dim3(256), 0, s, a)
 #define MR_SSGI(NT, CT)                \
     do {                               \
         if (al) {                      \

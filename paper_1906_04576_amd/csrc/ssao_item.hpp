@@ -183,7 +183,7 @@ template <typename NT, bool KLDS, bool AL>
 __device__ __forceinline__ void ssao_items(const SsaoArgs& a, const float* ks, const float* rows, float kmax) {
     const ItemMap m = make_item_map(a.c);
     const unsigned total = item_total(m), nchunks = (total + 255) / 256;
-    const ChunkRange cr = !AL && one_dense_level(a.c) ? naive_chunk(nchunks) : chunk_range(nchunks);
+    const ChunkRange cr = AL ? chunk_range(nchunks) : level_chunks(nchunks);
     for (unsigned c = cr.first; c < cr.end; c += cr.step) {
         const unsigned item = c * 256u + threadIdx.x;
         if (item < total) ssao_item<NT, KLDS, AL>(a, m, item, ks, rows, kmax);

@@ -204,7 +204,7 @@ template <typename NT, typename CT, bool AL, typename KP>
 __device__ __forceinline__ void ssgi_items(const SsgiArgs& a, KP K, float kmax, const float* rows) {
     const ItemMap m = make_item_map(a.c);
     const unsigned total = item_total(m), nchunks = (total + 255) / 256;
-    const ChunkRange cr = !AL && one_dense_level(a.c) ? naive_chunk(nchunks) : chunk_range(nchunks);
+    const ChunkRange cr = AL ? chunk_range(nchunks) : level_chunks(nchunks);
     for (unsigned c = cr.first; c < cr.end; c += cr.step) {
         const unsigned item = c * 256u + threadIdx.x;
         if (item < total) ssgi_item<NT, CT, AL>(a, m, item, K, kmax, rows);
