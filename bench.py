@@ -43,7 +43,7 @@ SSAO_FP32_PER_TEXEL = 31
 # HBM bytes per launch of the dominant kernel from the FETCH_SIZE and
 # WRITE_SIZE counters (profiles/ssao_4k_hbm_counters.md), scaled by the
 # copy-kernel calibration
-TRAFFIC_BYTES = {"k_ssao_multi": 62807668}
+TRAFFIC_BYTES = {"k_ssao_multi": 62802949}
 # VALU wave instructions per launch (SQ_INSTS_VALU,
 # profiles/ssao_4k_eval_valu_issue.md) of the multi-resolution evaluation and
 # of the naive pass, which runs the same per-sample code densely over every
@@ -53,7 +53,7 @@ VALU_INSTS = {"k_ssao_multi": 19942273, "k_ssao_plain": 211636800}
 # the counters above hold for the kernels of this machine code only: the
 # SHA-256 of the gfx950 code built from k_ssao.hip (libmr.code.json) when
 # they were taken.  Any other code reports them as null.
-COUNTER_CODE = {"k_ssao_multi": ("k_ssao.hip", "191f69035d770423f352b6077680c910cd50ea5a84d37958cd8d18de4928e6f0")}
+COUNTER_CODE = {"k_ssao_multi": ("k_ssao.hip", "c3d1ec0bc24993b4fe28dcde96ab96a0f5701cc93b6ca918baf0a0843f4f222d")}
 
 
 def log(*a):
