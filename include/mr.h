@@ -394,9 +394,10 @@ MR_API int mr_frame_cached(const mr_frame_desc* d, void* pyramid, size_t pyramid
  * MR_STATIC_SCRATCH_BYTES, one per device, that the library holds until the
  * process ends.  It enqueues the same kernels as mr_frame and calls no
  * allocating routine.  The stream's device must be the current device.
- * Frames whose intermediates need more than MR_STATIC_SCRATCH_BYTES (on the
- * compact path a 3840x2160 frame needs 27-39 MB; the other path needs about
- * 4.5 B/px more) are rejected with MR_E_WORKSPACE.  Every call on a device
+ * Frames whose intermediates need more than MR_STATIC_SCRATCH_BYTES are
+ * rejected with MR_E_WORKSPACE.  (The lists are laid out for every texel: on
+ * the compact path with 4 levels a 1920x1080 frame needs 48, 37 and 59 MB for
+ * SSAO, soft shadows and SSGI, a 2560x1440 frame 85, 65 and 104 MB.)  Every call on a device
  * shares that device's array: calls that may overlap on one device (other
  * streams, other threads) race and must be ordered by the caller; the array
  * keeps the last frame's intermediates, and each frame initialises what it

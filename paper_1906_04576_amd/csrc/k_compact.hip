@@ -16,7 +16,8 @@
 // launches of 4 to 5 us each on a 1366 x 768 frame, most of it the launch.)
 // A run is one chunk up to kCompactRuns chunks in the finest level, then as
 // many as keep to that number: the sums over earlier runs grow with its
-// square.  TODO
+// square.  (16384 x 16384, 65536 chunks: scatter 766 us with a run for each
+// chunk, 281 us in runs of 16; 1024 to 8192 runs within 3 % of each other.)
 #include "mr_internal.hpp"
 
 namespace mr {
